@@ -1589,118 +1589,204 @@ hipError_t launch_march_probe(const KParams &p, int layout, int grid, int block,
 }
 
 // ------------------------------------------------------------------ eq. (7)
-// Deterministic primary: the expected primary tally per emitted photon, one
-// thread per pixel.  The pixel is integrated over sub x sub sub-pixel rays from
-// the source (midpoint rule, d(Omega) = cos(gamma) dA / R^2 over the cone's
-// Omega = 2 pi (1 - cos(theta_max))); each ray is marched with the transport's
-// step rule (nominal step centres re-anchored every 4 steps, last step clipped)
-// and collects rho * length per material in the lane's LDS column (fp64); the
-// spectrum sum uses per bin the draw probability times eta(E) (bin_w) and mu
-// per unit density per material (bin_mu, [n_bins][n_mat]), both from the host.
-template <int MODE>
-__global__ void __launch_bounds__(128) primary_kernel(const KParams p, int sub,
+// Deterministic primary: the expected primary tally per emitted photon.  Each
+// pixel is integrated over sub x sub sub-pixel rays from the source (midpoint
+// rule, d(Omega) = cos(gamma) dA / R^2 over the cone's Omega =
+// 2 pi (1 - cos(theta_max))); each ray is marched with the transport's step
+// rule (nominal step centres re-anchored every 4 steps, last step clipped) and
+// collects rho * length per material (fp64); the spectrum sum uses per bin the
+// draw probability times eta(E) (bin_w) and mu per unit density per material
+// (bin_mu, [n_bins][n_mat]), both from the host.
+//
+// Latency bounds it at the usual panel sizes (128^2 pixels x 4 rays are 1024
+// waves).  A thread per pixel left three quarters of the chip idle and waited
+// for every step's gather and sum in turn (233 us for that panel through 64^3,
+// 119 bins).  A block takes 64 rays: its four waves each march a quarter of
+// the rays' steps in groups of 8 gathers, adding to their own columns with LDS
+// atomics that return nothing, and each evaluate a quarter of the bins; the
+// parts are added in a fixed order, and a pixel's rays in row order: 25 us,
+// with the registers held to four waves a SIMD, which the 1024 blocks then fill
+// at once (three: 31 us; eight parts: 40 us).
+constexpr int kPrimRays = 64;     // rays of a block at a time, one per lane
+constexpr int kPrimParts = 4;     // waves: shares of the steps and of the bins
+
+// exp(-t) for 0 <= t, within an ulp of fp64: t = n ln 2 - r with |r| <= ln(2) / 2
+// (ln 2 in two parts, the first with trailing zeros so that n times it is
+// exact) and the Taylor series of exp(r) to r^13 (its remainder is below
+// 2^-57).  Half the instructions of the library's exp, which also serves
+// arguments that do not occur here.
+__device__ __forceinline__ double exp_neg(double t) {
+    t = fmin(t, 800.0);                         // underflows to zero from 746 on
+    const double n = __builtin_rint(t * 1.4426950408889634);
+    double r = __builtin_fma(n, 0x1.62e42fefap-1, -t);
+    r = __builtin_fma(n, 0x1.cf79abc9e3b3ap-40, r);
+    constexpr double c[14] = {1.0, 1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720,
+                              1.0 / 5040, 1.0 / 40320, 1.0 / 362880, 1.0 / 3628800,
+                              1.0 / 39916800, 1.0 / 479001600, 1.0 / 6227020800.0};
+    double e = c[13];
+#pragma unroll
+    for (int k = 12; k >= 0; --k) e = __builtin_fma(e, r, c[k]);
+    return __builtin_ldexp(e, -(int)n);
+}
+
+// pixels of a block: whole pixels' rays in 64 lanes, or one pixel in rounds
+__host__ __device__ inline int primary_pixels(int sub) {
+    return sub * sub < kPrimRays ? kPrimRays / (sub * sub) : 1;
+}
+
+template <int MODE, int MAXM>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) primary_kernel(const KParams p, int sub,
                                                       const double *bin_w, const float *bin_mu,
                                                       int n_bins, float *out) {
     extern __shared__ double plds[];
     float *s_pal_rho = (float *)plds;                     // [256]
     uint8_t *s_pal_id = (uint8_t *)(s_pal_rho + 256);     // [256]
-    double *lam = plds + 160 + threadIdx.x;               // [n_mat] with stride blockDim
-    const int bs = blockDim.x;
+    double *s_val = plds + 160;                           // [kPrimParts][kPrimRays]
+    double *s_lam = s_val + kPrimParts * kPrimRays;       // [kPrimParts][n_mat][kPrimRays]
+    const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
+    double *lam = s_lam + (size_t)part * p.n_mat * kPrimRays + lane;
     if (MODE != kGeneric) {
-        for (int i = threadIdx.x; i < p.G.n_pal; i += bs) {
+        for (int i = threadIdx.x; i < p.G.n_pal; i += 256) {
             s_pal_rho[i] = p.G.pal_rho[i];
             s_pal_id[i] = p.G.pal_id[i];
         }
     }
     __syncthreads();
-    const int pix = blockIdx.x * bs + threadIdx.x;
-    if (pix >= p.nu * p.nv) return;
-    const int iu = pix % p.nu, iv = pix / p.nu;
     const ProjFrame &F = p.F;
     const VoxelGrid &gr = p.G;
+    const int rays = sub * sub, per_block = primary_pixels(sub);
     const double da = (double)p.pu * (double)p.pv / ((double)sub * sub);
-    double acc = 0.0;
-    for (int b = 0; b < sub; ++b)
-        for (int a = 0; a < sub; ++a) {
-            const double u = -(double)F.hu + ((double)iu + (a + 0.5) / sub) * p.pu;
-            const double v = -(double)F.hv + ((double)iv + (b + 0.5) / sub) * p.pv;
-            double w[3], r2 = 0.0, ax = 0.0;
+    const int pix0 = blockIdx.x * per_block;
+    const int n_pix = min(per_block, p.nu * p.nv - pix0);
+    double acc = 0.0;       // of pixel pix0 + lane, on the first wave
+    for (int r0 = 0; r0 < rays; r0 += kPrimRays) {
+        // this lane's pixel and ray
+        const int mine = per_block > 1 ? lane / rays : 0;
+        const int ray = per_block > 1 ? lane - mine * rays : r0 + lane;
+        const bool live = mine < n_pix && ray < rays;
+        const int pix = pix0 + (live ? mine : 0);
+        const int iu = pix % p.nu, iv = pix / p.nu;
+        const int b = live ? ray / sub : 0, a = live ? ray - b * sub : 0;
+        const double u = -(double)F.hu + ((double)iu + (a + 0.5) / sub) * p.pu;
+        const double v = -(double)F.hv + ((double)iv + (b + 0.5) / sub) * p.pv;
+        double w[3], r2 = 0.0, ax = 0.0;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            w[k] = ((double)F.D[k] + u * F.eu[k] + v * F.ev[k]) - (double)F.S[k];
+            r2 += w[k] * w[k];
+        }
+        const double R = sqrt(r2);
+        float d[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            d[k] = (float)(w[k] / R);
+            ax += w[k] / R * (double)F.ax[k];
+        }
+        for (int m = 0; m < p.n_mat; ++m) lam[m * kPrimRays] = 0.0;
+        float tin, tout;
+        if (live && box_entry(gr, F.S, d, tin, tout)) {
+            float c0[3], G[3], q[3];
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                w[k] = ((double)F.D[k] + u * F.eu[k] + v * F.ev[k]) - (double)F.S[k];
-                r2 += w[k] * w[k];
+                const float pin = F.S[k] + d[k] * tin;
+                G[k] = (d[k] * gr.inv_h) * p.step;
+                c0[k] = (pin - gr.lo[k]) * gr.inv_h + 0.5f * G[k];
             }
-            const double R = sqrt(r2);
-            float d[3];
+            const float L = tout - tin;
+            // a quarter of the steps, from an anchor
+            const uint32_t n = step_count(L, p.step);
+            const uint32_t share = ((n + 4 * kPrimParts - 1) / (4 * kPrimParts)) * 4;
+            const uint32_t k1 = min(n, (part + 1) * share);
+            for (uint32_t k = part * share; k < k1; k += kPrefetch) {
+                uint32_t code[kPrefetch];
+                float rho[kPrefetch];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                d[k] = (float)(w[k] / R);
-                ax += w[k] / R * (double)F.ax[k];
-            }
-            for (int m = 0; m < p.n_mat; ++m) lam[m * bs] = 0.0;
-            float tin, tout;
-            if (box_entry(gr, F.S, d, tin, tout)) {
-                float c0[3], G[3], q[3];
+                for (int s = 0; s < kPrefetch; ++s) {
 #pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    const float pin = F.S[k] + d[k] * tin;
-                    G[k] = (d[k] * gr.inv_h) * p.step;
-                    c0[k] = (pin - gr.lo[k]) * gr.inv_h + 0.5f * G[k];
-                    q[k] = c0[k];
-                }
-                const float L = tout - tin;
-                for (uint32_t k = 0;; ++k) {
-                    const float a0 = (float)k * p.step;
-                    if (!(a0 < L)) break;
-                    if ((k & 3u) == 0u) {
-#pragma unroll
-                        for (int t = 0; t < 3; ++t) q[t] = c0[t] + (float)k * G[t];
-                    } else {
-#pragma unroll
-                        for (int t = 0; t < 3; ++t) q[t] = q[t] + G[t];
-                    }
+                    for (int t = 0; t < 3; ++t)
+                        q[t] = s % 4 == 0 ? c0[t] + (float)(k + s) * G[t] : q[t] + G[t];
                     const uint32_t off = brick_offset(gr, voxel_index(q[0], gr.cmax[0]),
                                                       voxel_index(q[1], gr.cmax[1]),
                                                       voxel_index(q[2], gr.cmax[2]));
-                    const uint32_t code = dev(gr.vox)[off];
-                    float rho;
-                    int id;
-                    if (MODE == kGeneric) {
-                        rho = dev(gr.vrho)[off];
-                        id = (int)code;
-                    } else {
-                        rho = s_pal_rho[code];
-                        id = s_pal_id[code];
+                    code[s] = dev(gr.vox)[off];
+                    if (MODE == kGeneric) rho[s] = dev(gr.vrho)[off];
+                }
+#pragma unroll
+                for (int s = 0; s < kPrefetch; ++s) {
+                    const float a0 = (float)(k + s) * p.step;
+                    double len = (float)(k + s + 1u) * p.step < L ? (double)p.step
+                                                                   : (double)(L - a0);
+                    if (k + s >= k1) len = 0.0;           // past this part's share
+                    uint32_t id = code[s];
+                    if (MODE != kGeneric) {
+                        rho[s] = s_pal_rho[code[s]];
+                        id = s_pal_id[code[s]];
                     }
-                    const double len =
-                        (float)(k + 1u) * p.step < L ? (double)p.step : (double)(L - a0);
-                    lam[id * bs] += (double)rho * len;
+                    __hip_atomic_fetch_add(lam + id * kPrimRays, (double)rho[s] * len,
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 }
             }
-            double e_sum = 0.0;
-            for (int k = 0; k < n_bins; ++k) {
-                double tau = 0.0;
-                for (int m = 0; m < p.n_mat; ++m)
-                    tau += lam[m * bs] * (double)bin_mu[k * p.n_mat + m];
-                e_sum += bin_w[k] * exp(-tau);
-            }
-            acc += e_sum * (ax * da / r2);
         }
-    out[pix] = (float)(acc / (6.283185307179586 * (double)F.omc));
+        __syncthreads();
+        // the ray's whole path per material, and this wave's share of the bins
+        double path[MAXM];
+#pragma unroll
+        for (int m = 0; m < MAXM; ++m) {
+            path[m] = 0.0;
+            if (m < p.n_mat)
+#pragma unroll
+                for (int t = 0; t < kPrimParts; ++t)
+                    path[m] += s_lam[(t * p.n_mat + m) * kPrimRays + lane];
+        }
+        double e_sum = 0.0;
+        const int bins = (n_bins + kPrimParts - 1) / kPrimParts;
+        const int b1 = min(n_bins, (part + 1) * bins);
+#pragma unroll 4
+        for (int k = part * bins; k < b1; ++k) {
+            // MAXM loads without a branch (the surplus ones meet a zero path),
+            // so that several bins' are in flight
+            double tau = 0.0;
+#pragma unroll
+            for (int m = 0; m < MAXM; ++m)
+                tau = __builtin_fma(path[m], (double)bin_mu[k * p.n_mat + (m < p.n_mat ? m : 0)],
+                                    tau);
+            e_sum = __builtin_fma(bin_w[k], exp_neg(tau), e_sum);
+        }
+        s_val[part * kPrimRays + lane] = e_sum * (ax * da / r2);
+        __syncthreads();
+        if (part == 0 && lane < n_pix) {
+            const int first = per_block > 1 ? lane * rays : 0;
+            const int count = per_block > 1 ? rays : min(kPrimRays, rays - r0);
+            for (int t = 0; t < count; ++t) {
+                double ray_sum = 0.0;
+#pragma unroll
+                for (int q = 0; q < kPrimParts; ++q) ray_sum += s_val[q * kPrimRays + first + t];
+                acc += ray_sum;
+            }
+        }
+    }
+    if (part == 0 && lane < n_pix)
+        out[pix0 + lane] = (float)(acc / (6.283185307179586 * (double)F.omc));
 }
 
 hipError_t launch_primary(const KParams &p, int sub, const double *bin_w, const float *bin_mu,
                           int n_bins, float *out, hipStream_t stream) {
-    const int block = 128;
-    const int grid = (p.nu * p.nv + block - 1) / block;
-    const size_t lds = 160 * sizeof(double) + (size_t)p.n_mat * block * sizeof(double);
+    const int per_block = primary_pixels(sub);
+    const int grid = (p.nu * p.nv + per_block - 1) / per_block;
+    const size_t lds = (160 + (size_t)kPrimParts * kPrimRays * (1 + p.n_mat)) * sizeof(double);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), lds, stream, p, sub, bin_w, bin_mu,
+                           n_bins, out);
+        return hipGetLastError();
+    };
+    // the default set has 5 materials; each of the 16 possible ones would hold
+    // two registers of path
+    const bool few = p.n_mat <= 5;
     if (p.G.layout == kGeneric)
-        hipLaunchKernelGGL(primary_kernel<kGeneric>, dim3(grid), dim3(block), lds, stream, p, sub,
-                           bin_w, bin_mu, n_bins, out);
-    else
-        hipLaunchKernelGGL(primary_kernel<kPaletteLane>, dim3(grid), dim3(block), lds, stream, p,
-                           sub, bin_w, bin_mu, n_bins, out);
-    return hipGetLastError();
+        return few ? launch(primary_kernel<kGeneric, 5>)
+                   : launch(primary_kernel<kGeneric, kMaxMaterials>);
+    return few ? launch(primary_kernel<kPaletteLane, 5>)
+               : launch(primary_kernel<kPaletteLane, kMaxMaterials>);
 }
 
 // Angular interpolation (section II-C-3): scatter maps simulated at every
