@@ -1,6 +1,8 @@
 // Launch parameters shared by the transport kernels and the host runtime.
 #pragma once
 
+#include <hip/hip_runtime.h>
+
 #include <cstdint>
 
 namespace mcx {
@@ -89,8 +91,10 @@ struct JobDesc {
 struct KParams {
     // voxel object (single projection)
     VoxelGrid G;
-    // tables: [n_mat][J] mu/rho on E_j = 1 + j keV, eta[J]
-    const float *pe, *coh, *inc, *eta;
+    // tables on E_j = 1 + j keV: mu/rho [J][n_mat] (photoelectric, Rayleigh, Compton, 0),
+    // eta[J]
+    const float4 *mu4;
+    const float *eta;
     int J, n_mat;
     const double *rayl_b;      // [n_mat] Rayleigh screening constants
     const double *pz_scale;    // [n_mat] Compton-profile momentum scale / (m c)
@@ -102,7 +106,8 @@ struct KParams {
     // panel and march
     ProjFrame F;
     float sdd, pu, pv, step;
-    int nu, nv, snu, snv, bu, bv;   // bu = nu / snu, bv = nv / snv
+    int nu, nv, snu, snv;
+    float inv_bu, inv_bv;           // snu / nu, snv / nv: one over the scatter bins' pixels
     uint32_t flags;
     // work
     uint64_t first, n;

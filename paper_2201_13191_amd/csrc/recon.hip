@@ -9,6 +9,8 @@
 
 #include <cstdint>
 
+#include "fp64_math.hpp"
+
 namespace mcx {
 
 struct FdkGeom {
@@ -39,22 +41,6 @@ __global__ void scatter_correct_kernel(const float *a, const float *ip, const fl
 }
 
 typedef __attribute__((__vector_size__(4 * sizeof(double)))) double f64x4;
-
-// 1 / x to an ulp or two of fp64, for x away from zero and the range's ends
-// (two Newton steps on the hardware's estimate)
-__device__ __forceinline__ double fast_rcp(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    r = __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
-    return __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
-}
-
-// 1 / sqrt(x) likewise
-__device__ __forceinline__ double fast_rsqrt(double x) {
-    double r = __builtin_amdgcn_rsq(x);
-    const double hx = 0.5 * x;
-    r = __builtin_fma(r, __builtin_fma(-hx * r, r, 0.5), r);
-    return __builtin_fma(r, __builtin_fma(-hx * r, r, 0.5), r);
-}
 
 // The cosine weight of panel column k on the virtual panel through the axis
 // (coordinates scaled by s = R / D): R / sqrt(R^2 + a^2 + b^2).

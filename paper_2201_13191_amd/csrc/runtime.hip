@@ -169,7 +169,8 @@ struct mc_ctx {
     std::vector<float> pe, coh, inc, eta;
     void *d_tables = nullptr;
     size_t d_tables_bytes = 0;
-    const float *dp_pe = nullptr, *dp_coh = nullptr, *dp_inc = nullptr, *dp_eta = nullptr;
+    const float4 *dp_mu4 = nullptr;
+    const float *dp_eta = nullptr;
     const float *dp_ebin = nullptr;
     const uint64_t *dp_thr = nullptr;
     const uint32_t *dp_guide = nullptr;
@@ -263,14 +264,14 @@ mc_status refresh_tables(mc_ctx *c, bool may_alloc = true) {
     build_tables(mm.data(), n_mat, J, c->eta_user.empty() ? nullptr : c->eta_user.data(),
                  (int)c->eta_user.size(), c->pe, c->coh, c->inc, c->eta);
     c->J = J;
-    // blob: rb[n_mat] f64 | pz[n_mat] f64 | kn[kKnTerms] f64 | coh series[kCohTerms] f64 |
-    //       thr[n_bins] u64 | pe | coh | inc [n_mat*J] | eta[J] | e_bin[n_bins] |
-    //       guide[256] u32
+    // blob: mu4[J][n_mat] (pe, coh, inc, 0) f32 | rb[n_mat] f64 | pz[n_mat] f64 |
+    //       kn[kKnTerms] f64 | coh series[kCohTerms] f64 | thr[n_bins] u64 | eta[J] |
+    //       e_bin[n_bins] | guide[256] u32
     const size_t nb = c->e_bin.size();
     const size_t tab = (size_t)n_mat * J;
     //       | bin_w[n_bins] f64 | bin_mu[n_bins][n_mat] f32 (the deterministic primary)
-    const size_t head = (size_t)(2 * n_mat + kKnTerms + kCohTerms) * 8;
-    const size_t body = nb * 8 + (3 * tab + J + nb + 256) * 4;
+    const size_t head = tab * 16 + (size_t)(2 * n_mat + kKnTerms + kCohTerms) * 8;
+    const size_t body = nb * 8 + (J + nb + 256) * 4;
     const size_t bins_off = ((head + body + 7) / 8) * 8;
     const size_t bytes = bins_off + nb * 8 + nb * n_mat * 4;
     double kn[kKnTerms], cohs[kCohTerms];
@@ -309,14 +310,21 @@ mc_status refresh_tables(mc_ctx *c, bool may_alloc = true) {
         std::memcpy(blob.data() + off, src, n);
         off += n;
     };
+    std::vector<float> mu4(tab * 4, 0.0f);
+    for (int j = 0; j < J; ++j)
+        for (int m = 0; m < n_mat; ++m) {
+            float *q = mu4.data() + ((size_t)j * n_mat + m) * 4;
+            const size_t t = (size_t)m * J + j;
+            q[0] = c->pe[t];
+            q[1] = c->coh[t];
+            q[2] = c->inc[t];
+        }
+    put(mu4.data(), tab * 16);
     put(c->rayl_b.data(), n_mat * 8);
     put(c->pz_scale.data(), n_mat * 8);
     put(kn, sizeof kn);
     put(cohs, sizeof cohs);
     put(c->thr.data(), nb * 8);
-    put(c->pe.data(), tab * 4);
-    put(c->coh.data(), tab * 4);
-    put(c->inc.data(), tab * 4);
     put(c->eta.data(), (size_t)J * 4);
     put(c->e_bin.data(), nb * 4);
     put(guide, sizeof guide);
@@ -336,18 +344,16 @@ mc_status refresh_tables(mc_ctx *c, bool may_alloc = true) {
     }
     HIP_TRY(c, hipMemcpy(c->d_tables, blob.data(), bytes, hipMemcpyHostToDevice));
     unsigned char *b = (unsigned char *)c->d_tables;
-    c->dp_rb = (const double *)b;
-    c->dp_pz = (const double *)b + n_mat;
-    c->dp_kn = (const double *)b + 2 * n_mat;
-    c->dp_coh_series = (const double *)b + 2 * n_mat + kKnTerms;
+    c->dp_mu4 = (const float4 *)b;
+    c->dp_rb = (const double *)(b + tab * 16);
+    c->dp_pz = c->dp_rb + n_mat;
+    c->dp_kn = c->dp_rb + 2 * n_mat;
+    c->dp_coh_series = c->dp_rb + 2 * n_mat + kKnTerms;
     c->dp_thr = (const uint64_t *)(b + head);
     const float *f = (const float *)(b + head + nb * 8);
-    c->dp_pe = f;
-    c->dp_coh = f + tab;
-    c->dp_inc = f + 2 * tab;
-    c->dp_eta = f + 3 * tab;
-    c->dp_ebin = f + 3 * tab + J;
-    c->dp_guide = (const uint32_t *)(f + 3 * tab + J + nb);
+    c->dp_eta = f;
+    c->dp_ebin = f + J;
+    c->dp_guide = (const uint32_t *)(f + J + nb);
     c->dp_bin_w = (const double *)(b + bins_off);
     c->dp_bin_mu = (const float *)(b + bins_off + nb * 8);
     c->tables_dirty = false;
@@ -432,7 +438,7 @@ mc_status check_overflow(mc_ctx *c, uint64_t n_max) {
 // Tables, panel and knobs shared by single and batched launches.
 void common_params(mc_ctx *c, KParams &p) {
     std::memset(&p, 0, sizeof p);
-    p.pe = c->dp_pe; p.coh = c->dp_coh; p.inc = c->dp_inc; p.eta = c->dp_eta;
+    p.mu4 = c->dp_mu4; p.eta = c->dp_eta;
     p.J = c->J;
     p.n_mat = (int)c->mats.size();
     p.rayl_b = c->dp_rb;
@@ -445,7 +451,8 @@ void common_params(mc_ctx *c, KParams &p) {
     const mc_geometry &g = c->g;
     p.sdd = g.sdd_mm; p.pu = g.pu_mm; p.pv = g.pv_mm; p.step = g.step_mm;
     p.nu = g.nu; p.nv = g.nv; p.snu = g.snu; p.snv = g.snv;
-    p.bu = g.nu / g.snu; p.bv = g.nv / g.snv;
+    p.inv_bu = 1.0f / (float)(g.nu / g.snu);
+    p.inv_bv = 1.0f / (float)(g.nv / g.snv);
     p.flags = g.flags;
     p.event_batch = c->event_batch > 0 ? c->event_batch : kDefaultEventBatch;
     p.stats = c->d_ctl + kRing;

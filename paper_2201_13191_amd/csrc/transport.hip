@@ -22,6 +22,7 @@
 // wave or round runs it, and images do not depend on the launch shape.
 #include <hip/hip_runtime.h>
 
+#include "fp64_math.hpp"
 #include "kernel_params.hpp"
 
 namespace mcx {
@@ -59,17 +60,22 @@ struct StreamT {
     uint32_t w0, w1, w2, w3;
     uint32_t n, tag;   // PSEUDO only
 
-    __device__ void reset(uint64_t photon, uint32_t k0, uint32_t k1) {
-        id_lo = (uint32_t)photon;
-        id_hi = (uint32_t)(photon >> 32);
+    // the key is set apart from the photon: one of a whole launch stays uniform
+    // (scalar registers, its schedule on the scalar unit)
+    __device__ void keys(uint32_t k0, uint32_t k1) {
         key0 = k0;
         key1 = k1;
+    }
+    __device__ void reset(uint64_t photon) {
+        id_lo = (uint32_t)photon;
+        id_hi = (uint32_t)(photon >> 32);
         next = 0;
         cached = 0xFFFFFFFFu;
     }
     __device__ void reset_pseudo(uint64_t photon, uint32_t k0, uint32_t k1, uint32_t scat,
                                  uint32_t i) {
-        reset(photon, k0, k1);
+        keys(k0, k1);
+        reset(photon);
         n = scat;
         tag = (i + 1u) << 12;
     }
@@ -148,64 +154,99 @@ __device__ __forceinline__ float grid_lerp(const float *t, int J, float e) {
     return t[j] + f * (t[j + 1] - t[j]);
 }
 
+// mu/rho of the three processes at energy e: entries j and j + 1 of the packed
+// table mu4[J][n_mat] (photoelectric, Rayleigh, Compton, -), each one 16-byte
+// load, interpolated as grid_lerp does
+struct MuAt {
+    const float4 *lo;
+    float f;
+    __device__ __forceinline__ MuAt(const KParams &p, float e) {
+        const float x = e - 1.0f;
+        int j = (int)x;
+        j = j < 0 ? 0 : (j > p.J - 2 ? p.J - 2 : j);
+        f = x - (float)j;
+        lo = p.mu4 + (uint32_t)(j * p.n_mat);
+    }
+    __device__ __forceinline__ void of(const KParams &p, int m, float &pe, float &coh,
+                                       float &inc) const {
+        const float4 a = lo[m], b = lo[m + p.n_mat];
+        pe = a.x + f * (b.x - a.x);
+        coh = a.y + f * (b.y - a.y);
+        inc = a.z + f * (b.z - a.z);
+    }
+};
+
 // per-lane linear attenuation per material at energy e, mm^-1 per g/cm^3
 __device__ __forceinline__ void material_mu(const KParams &p, float e, float *mm, int stride) {
+    const MuAt at(p, e);
     for (int m = 0; m < p.n_mat; ++m) {
-        const int o = m * p.J;
-        const float a = grid_lerp(p.pe + o, p.J, e);
-        const float b = grid_lerp(p.coh + o, p.J, e);
-        const float c = grid_lerp(p.inc + o, p.J, e);
+        float a, b, c;
+        at.of(p, m, a, b, c);
         mm[m * stride] = ((a + b) + c) * 0.1f;
     }
 }
 
 // ------------------------------------------------------------------ samplers
 // Rayleigh polar angle: v = sin^2(theta/2)/lambda^2 inverted from the
-// (1 + b v)^-4 form-factor weight, accepted with (1 + cos^2)/2 evaluated on
-// the fp32 cosine.  One trial (two draws); the cosine is set either way.
+// (1 + b v)^-4 form-factor weight, v = (y^(-1/3) - 1) / b, accepted with
+// (1 + cos^2)/2 evaluated on the fp32 cosine (two draws a trial).
 template <class S>
-__device__ __forceinline__ bool rayleigh_trial(S &s, float e, double b, float &cf) {
-    const double t = (double)e / 12.398419843320026;
+__device__ __forceinline__ float sample_rayleigh(S &s, float e, double b) {
+    const double t = div_const((double)e, 12.398419843320026, 1.0 / 12.398419843320026);
     const double V = t * t;
     const double W = 1.0 + b * V;
-    const double ymin = 1.0 / (W * W * W);
-    uint32_t w[2];
-    s.draw(w);
-    const double r1 = (double)unit_float(w[0]);
-    const double r2 = (double)unit_float(w[1]);
-    const double y = 1.0 - r1 * (1.0 - ymin);
-    const double v = (1.0 / cbrt(y) - 1.0) / b;
-    cf = (float)(1.0 - 2.0 * v / V);
-    const double cd = (double)cf;
-    return r2 <= 0.5 * (1.0 + cd * cd);
-}
-
-template <class S>
-__device__ float sample_rayleigh(S &s, float e, double b) {
-    float cf;
-    while (!rayleigh_trial(s, e, b, cf)) {
+    const double span = 1.0 - fast_rcp(W * W * W);       // 1 - (1 + b V)^-3
+    const double k2 = fast_div(2.0, b * V);              // cos = 1 - 2 v / V
+    for (;;) {
+        uint32_t w[2];
+        s.draw(w);
+        const double r1 = (double)unit_float(w[0]);
+        const double r2 = (double)unit_float(w[1]);
+        const float cf = (float)(1.0 - (rcp_cbrt(1.0 - r1 * span) - 1.0) * k2);
+        const double cd = (double)cf;
+        if (r2 <= 0.5 * (1.0 + cd * cd)) return cf;
     }
-    return cf;
 }
 
 // Kahn's rejection method for the Klein-Nishina polar angle: x = E / E_KN drawn
-// from one of two branches and accepted against the KN shape.  One trial
-// (three draws); false when rejected.
-__device__ __forceinline__ bool kahn_trial(PhotonStream &s, double a, double &x) {
-    const double top = 1.0 + 2.0 * a;
-    const double branch = top / (9.0 + 2.0 * a);
-    uint32_t w[3];
-    s.draw(w);
-    const double r1 = (double)unit_float(w[0]);
-    const double r2 = (double)unit_float(w[1]);
-    const double r3 = (double)unit_float(w[2]);
-    if (r1 <= branch) {
-        x = 1.0 + 2.0 * a * r2;
-        return r3 <= 4.0 * (1.0 / x - 1.0 / (x * x));
+// from one of two branches (x = 1 + 2 a r2, or (1 + 2 a) over that) and accepted
+// against the KN shape, three draws a trial.  A trial's acceptance is decided
+// with approximate reciprocals wherever it is not within 1e-9 of its draw --
+// their errors are below 1e-10 -- and by the correctly rounded expression
+// otherwise, so the decisions are those of the latter, at a third of its
+// instructions; x itself is made once, after the loop.
+__device__ __forceinline__ double sample_kahn(PhotonStream &s, double a) {
+    const double a2 = 2.0 * a;
+    const double top = 1.0 + a2;
+    const double branch = top / (9.0 + a2);
+    const double inv_a = fast_rcp(a), inv_top = fast_rcp(top);
+    double x1;
+    bool first;
+    for (;;) {
+        uint32_t w[3];
+        s.draw(w);
+        const double r1 = (double)unit_float(w[0]);
+        const double r2 = (double)unit_float(w[1]);
+        const double r3 = (double)unit_float(w[2]);
+        first = r1 <= branch;
+        x1 = 1.0 + a2 * r2;
+        double y = __builtin_amdgcn_rcp(x1);             // 1 / x1, x1 in [1, top]
+        y = __builtin_fma(__builtin_fma(-x1, y, 1.0), y, y);
+        const double c = 1.0 - (top * y - 1.0) * inv_a;
+        const double shape = first ? 4.0 * (y - y * y) : 0.5 * (c * c + x1 * inv_top);
+        bool take = r3 <= shape;
+        if (__builtin_fabs(shape - r3) < 1e-9) {
+            if (first) {
+                take = r3 <= 4.0 * (1.0 / x1 - 1.0 / (x1 * x1));
+            } else {
+                const double x = top / x1;
+                const double cx = 1.0 - (x - 1.0) / a;
+                take = r3 <= 0.5 * (cx * cx + 1.0 / x);
+            }
+        }
+        if (take) break;
     }
-    x = top / (1.0 + 2.0 * a * r2);
-    const double c = 1.0 - (x - 1.0) / a;
-    return r3 <= 0.5 * (c * c + 1.0 / x);
+    return first ? x1 : fast_div(top, x1);
 }
 
 // ------------------------------------------------------------------ binding effects
@@ -274,20 +315,18 @@ __device__ double sample_doppler(S &s, double pz, double ratio_kn, double om) {
 template <bool BIND>
 __device__ bool compton_collision(PhotonStream &s, const KParams &p, int mat, float e, float &ct,
                                   float &e_out) {
-    const double a = (double)e / 510.99895;
-    double x;
-    while (!kahn_trial(s, a, x)) {
-    }
+    const double a = div_const((double)e, 510.99895, 1.0 / 510.99895);
+    const double x = sample_kahn(s, a);
     if (BIND && (p.phys & 1u)) {
         const double t = (double)e / 12.398419843320026;
         const double u = (double)s.u();
         if (!(u <= incoh_sf(p.rayl_b[mat], t * t, (x - 1.0) / a))) return false;
     }
-    ct = (float)(1.0 - (x - 1.0) / a);
+    ct = (float)(1.0 - fast_div(x - 1.0, a));
     if (BIND && (p.phys & 2u))
         e_out = (float)((double)e * sample_doppler(s, p.pz_scale[mat], x, (x - 1.0) / a));
     else
-        e_out = (float)((double)e / x);
+        e_out = (float)fast_div((double)e, x);
     return true;
 }
 
@@ -397,13 +436,17 @@ __device__ __forceinline__ bool panel_hit(const KParams &p, const ProjFrame &F, 
     return true;
 }
 
+// i / b by inv = 1 / b (fp32): pixels are below 2^14, so (i + 1/2) / b is at least
+// 2^-15 from a whole number, and the product's error below 2^-9
+__device__ __forceinline__ int bin_of(int i, float inv) { return (int)(((float)i + 0.5f) * inv); }
+
 // birth direction inside the cone that circumscribes the panel: cos theta
 // uniform on [cos theta_max, 1], azimuth uniform (two draws)
 __device__ __forceinline__ void cone_direction(const ProjFrame &F, PhotonStream &rng, float d[3]) {
     const float ct = 1.0f - rng.u() * F.omc;
     const float stt = sqrtf(fmaxf(0.0f, 1.0f - ct * ct));
     double sphi, cphi;
-    sincos(6.283185307179586 * (double)rng.u(), &sphi, &cphi);
+    sincos_2pi(6.283185307179586 * (double)rng.u(), sphi, cphi);
     const float cp = (float)cphi, sp = (float)sphi;
 #pragma unroll
     for (int a = 0; a < 3; ++a) d[a] = (ct * F.ax[a] + (stt * cp) * F.eu[a]) + (stt * sp) * F.ev[a];
@@ -413,11 +456,11 @@ __device__ __forceinline__ void cone_direction(const ProjFrame &F, PhotonStream 
 enum : int { kStHist, kStSteps, kStFlights, kStPhoto, kStRayl, kStCompt, kStPrim, kStScat,
              kStCut, kStCap, kStSkipped, kStPdScores, kStPdKilled, kStPdSteps, kStNull, kStCount };
 
-// optical-depth increments on the grid of 2^-32: fp64 sums of them are exact,
-// so a run of equal increments can be added at once
-__device__ __forceinline__ double on_grid(double x) {
-    return __builtin_rint(x * 4294967296.0) * 2.3283064365386963e-10;
-}
+// Optical depths are counted in ticks of 2^-32: whole numbers in fp64, whose
+// sums are exact, so a run of equal increments can be added at once.  A full
+// step's increment at attenuation mu is rint(mu * step * 2^32).
+constexpr double kTick = 2.3283064365386963e-10;     // 2^-32
+constexpr double kTicks = 4294967296.0;
 
 constexpr float kSkipMargin = 1.0f / 64.0f;   // voxels kept from a uniform region's faces
 #ifndef MCX_MIN_SKIP
@@ -466,7 +509,7 @@ __device__ __forceinline__ uint32_t brick_offset(const VoxelGrid &p, uint32_t ix
 // (float)k * step < len (an increasing sequence), from the quotient's estimate
 __device__ __forceinline__ uint32_t step_count(float len, float step) {
     if (!(len > 0.0f)) return 0u;
-    uint32_t n = (uint32_t)(len / step);
+    uint32_t n = (uint32_t)(len * __builtin_amdgcn_rcpf(step));
     while (n > 0u && !((float)(n - 1u) * step < len)) --n;
     while ((float)n * step < len) ++n;
     return n;
@@ -527,7 +570,7 @@ transport_kernel(const KParams p) {
     float *mm = lds + kLdsHeader + threadIdx.x;
     double *inc_pal = (double *)(lds + kLdsHeader + p.n_mat * bs) + threadIdx.x;
     const uint32_t bs8 = (uint32_t)bs * 8u;   // byte stride between a lane's fp64 entries
-    const double step32 = (double)p.step * 4294967296.0;
+    const double step32 = (double)p.step * kTicks;
     const int lane = (int)__lane_id();
     if (!BATCH && MODE != kGeneric) {
         for (int i = threadIdx.x; i < p.G.n_pal; i += bs) {
@@ -643,15 +686,17 @@ transport_kernel(const KParams p) {
             for (int c = 0; c < gr.n_pal; ++c) {
                 const int id = (int)((ids[c >> 2] >> (8 * (c & 3))) & 0xFFu);
                 const float mu = rho[c] * mm[id * bs];
-                inc_pal[c * bs] = __builtin_rint((double)mu * step32) * 2.3283064365386963e-10;
+                inc_pal[c * bs] = __builtin_rint((double)mu * step32);
             }
         }
     };
     // a new photon: energy bin, direction in the cone, position at the source
+    if (!BATCH) rng.keys(p.key0, p.key1);
     auto birth = [&](uint64_t photon, uint32_t k0, uint32_t k1, const ProjFrame &F)
         __attribute__((always_inline)) {
         pid = photon;
-        rng.reset(pid, k0, k1);
+        if (BATCH) rng.keys(k0, k1);
+        rng.reset(pid);
         // the first block: energy bin, the cone's polar cosine and azimuth,
         // and the first flight's optical depth
         uint32_t w[4];
@@ -696,7 +741,7 @@ transport_kernel(const KParams p) {
             G[a] = (dir[a] * gr.inv_h) * p.step;
             c0[a] = (pin - gr.lo[a]) * gr.inv_h + 0.5f * G[a];
             q[a] = c0[a] + 0.0f * G[a];
-            ig[a] = 1.0f / G[a];
+            ig[a] = __builtin_amdgcn_rcpf(G[a]);   // only bounds run lengths, by a margin
         }
         const float len = tout - tin;
         nsteps = step_count(len, p.step);
@@ -710,10 +755,8 @@ transport_kernel(const KParams p) {
     // the interaction type at (material, E): 0 photoelectric (or any
     // interaction without scattering), 1 Rayleigh, 2 Compton
     auto interaction_type = [&]() __attribute__((always_inline)) -> int {
-        const int off = mat * p.J;
-        const float a = grid_lerp(p.pe + off, p.J, e);
-        const float b = grid_lerp(p.coh + off, p.J, e);
-        const float c = grid_lerp(p.inc + off, p.J, e);
+        float a, b, c;
+        MuAt(p, e).of(p, mat, a, b, c);
         const float tot = (a + b) + c;
         const float xs = rng.u() * tot;
         if ((p.flags & 1u) || xs < a) {
@@ -773,7 +816,7 @@ transport_kernel(const KParams p) {
     // false when the pseudo-particle needs none (killed, below 1 keV, or
     // scored at once because it leaves the object without a step).
     auto pd_score = [&](double tau_chord) __attribute__((always_inline)) {
-        const double x = pd_x0 * exp(-tau_chord);
+        const double x = pd_x0 * exp_neg(tau_chord * kTick);
         const long long t = (long long)__builtin_rint(x * 1048576.0);
         if (t != 0)
             __hip_atomic_fetch_add(dev_rw(p.scat) + pd_bin, (unsigned long long)t,
@@ -791,7 +834,7 @@ transport_kernel(const KParams p) {
                             (uint32_t)pd_i);
             const float ct = sample_rayleigh(ps, e, p.rayl_b[mat]);
             double sphi, cphi;
-            sincos(6.283185307179586 * (double)ps.u(), &sphi, &cphi);
+            sincos_2pi(6.283185307179586 * (double)ps.u(), sphi, cphi);
             float om[3] = {d[0], d[1], d[2]};
             rotate_direction(om[0], om[1], om[2], ct, sqrtf(fmaxf(0.0f, 1.0f - ct * ct)),
                              (float)cphi, (float)sphi);
@@ -808,7 +851,7 @@ transport_kernel(const KParams p) {
                 }
             }
             pd_x0 = x0;
-            pd_bin = (uint32_t)((iv / p.bv) * p.snu + iu / p.bu);
+            pd_bin = (uint32_t)(bin_of(iv, p.inv_bv) * p.snu + bin_of(iu, p.inv_bu));
             float tout;
             if (!box_entry(p.G, o, om, tin, tout)) {
                 pd_score(0.0);
@@ -889,7 +932,7 @@ transport_kernel(const KParams p) {
             }
         }
         pd_x0 = x0;
-        pd_bin = (uint32_t)((iv / p.bv) * p.snu + iu / p.bu);
+        pd_bin = (uint32_t)(bin_of(iv, p.inv_bv) * p.snu + bin_of(iu, p.inv_bu));
         float om[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) om[a] = (float)((double)dq[a] / dist);
@@ -974,7 +1017,7 @@ transport_kernel(const KParams p) {
                 } else {
                     // with the point detector the scatter image holds its scores only
                     if (!PD) {
-                        const int su = iu / p.bu, sv = iv / p.bv;
+                        const int su = bin_of(iu, p.inv_bu), sv = bin_of(iv, p.inv_bv);
                         __hip_atomic_fetch_add(dev_rw(scat) + (size_t)sv * p.snu + su,
                                                (unsigned long long)t, __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_AGENT);
@@ -1033,10 +1076,10 @@ transport_kernel(const KParams p) {
             }
             if (!alive) {
                 const uint64_t rank = (uint64_t)__popcll(dead & ((1ull << lane) - 1ull));
-                if (rank < avail)
-                    birth(p.first + res_next + rank, p.key0, p.key1, p.F);
-                else if (rank - avail < ce - cb)
-                    birth(p.first + cb + (rank - avail), p.key0, p.key1, p.F);
+                const bool kept = rank < avail;
+                if (kept || rank - avail < ce - cb)
+                    birth(p.first + (kept ? res_next + rank : cb + (rank - avail)), p.key0,
+                          p.key1, p.F);
             }
             if (avail >= nd) {
                 res_next += nd;
@@ -1093,7 +1136,7 @@ transport_kernel(const KParams p) {
         float cp = 0.0f, sp = 0.0f, stt = 0.0f;
         if (turn) {
             double sphi, cphi;
-            sincos(6.283185307179586 * (double)unit_float(phi_w), &sphi, &cphi);
+            sincos_2pi(6.283185307179586 * (double)unit_float(phi_w), sphi, cphi);
             cp = (float)cphi;
             sp = (float)sphi;
             stt = sqrtf(fmaxf(0.0f, 1.0f - dir_ct * dir_ct));
@@ -1116,7 +1159,7 @@ transport_kernel(const KParams p) {
                     refresh_mu(e, gr);
                     tab_e = e;
                 }
-                ts = (double)(float)(-log((double)unit_float((uint32_t)ts)));
+                ts = (double)(float)neg_log(unit_float((uint32_t)ts)) * kTicks;
                 start_march(gr, d, tout);
                 if (STATS) ++st[kStFlights];
             } else {
@@ -1204,7 +1247,7 @@ transport_kernel(const KParams p) {
                         const uint32_t id = lds_pal ? (uint32_t)s_pal_id[c]
                                                     : (uint32_t)dev(gl.pal_id)[c];
                         const float mu = rho * mm[id * bs];
-                        inc = __builtin_rint((double)mu * step32) * 2.3283064365386963e-10;
+                        inc = __builtin_rint((double)mu * step32);
                     }
                     const double tn = tau + (double)cnt * inc;
                     if (tn >= ts) {
@@ -1329,7 +1372,7 @@ transport_kernel(const KParams p) {
                         id = BATCH ? dev(gl.pal_id)[code[u]] : s_pal_id[code[u]];
                     }
                     const float mu = rho * mm[id * bs];
-                    return __builtin_rint((double)mu * step32) * 2.3283064365386963e-10;
+                    return __builtin_rint((double)mu * step32);
                 });
             }
             if (PD && pd_flight) {
@@ -1337,7 +1380,7 @@ transport_kernel(const KParams p) {
                     // the chord's last step was in this group: add it, clipped
                     double r = (double)last / (double)p.step;
                     r = r > 1.0 ? 1.0 : r;
-                    tau = tau + on_grid(inc_last * r);
+                    tau = tau + __builtin_rint(inc_last * r);
                     k = nsteps;
                     event = 3;
                     flying = false;
@@ -1352,7 +1395,7 @@ transport_kernel(const KParams p) {
                     // photon may leave the object instead
                     double r = (double)last / (double)p.step;
                     r = r > 1.0 ? 1.0 : r;
-                    const double inc_l = on_grid(inc_hit * r);
+                    const double inc_l = __builtin_rint(inc_hit * r);
                     if (tau + inc_l >= ts) {
                         interact(code_hit, inc_l, last, false);
                     } else {
@@ -1429,7 +1472,8 @@ __global__ void __launch_bounds__(256) march_probe_kernel(const KParams p,
                     (unsigned long long)__popcll(dead & ((1ull << lane) - 1ull));
                 if (rank < got) {
                     PhotonStream rng;
-                    rng.reset(p.first + base + rank, p.key0, p.key1);
+                    rng.keys(p.key0, p.key1);
+                    rng.reset(p.first + base + rank);
                     (void)rng.raw();                       // the energy draw
                     float o[3], d[3], tin, tout;
                     cone_direction(p.F, rng, d);
@@ -1498,7 +1542,8 @@ __global__ void sample_kernel(const KParams p, int process, int material, float 
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     PhotonStream s;
-    s.reset(i, p.key0, p.key1);
+    s.keys(p.key0, p.key1);
+    s.reset(i);
     if (process == 0) {
         e_out[i] = p.e_bin[pick_bin(p, s.raw())];
     } else if (process == 3) {
@@ -1609,25 +1654,6 @@ hipError_t launch_march_probe(const KParams &p, int layout, int grid, int block,
 // at once (three: 31 us; eight parts: 40 us).
 constexpr int kPrimRays = 64;     // rays of a block at a time, one per lane
 constexpr int kPrimParts = 4;     // waves: shares of the steps and of the bins
-
-// exp(-t) for 0 <= t, within an ulp of fp64: t = n ln 2 - r with |r| <= ln(2) / 2
-// (ln 2 in two parts, the first with trailing zeros so that n times it is
-// exact) and the Taylor series of exp(r) to r^13 (its remainder is below
-// 2^-57).  Half the instructions of the library's exp, which also serves
-// arguments that do not occur here.
-__device__ __forceinline__ double exp_neg(double t) {
-    t = fmin(t, 800.0);                         // underflows to zero from 746 on
-    const double n = __builtin_rint(t * 1.4426950408889634);
-    double r = __builtin_fma(n, 0x1.62e42fefap-1, -t);
-    r = __builtin_fma(n, 0x1.cf79abc9e3b3ap-40, r);
-    constexpr double c[14] = {1.0, 1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720,
-                              1.0 / 5040, 1.0 / 40320, 1.0 / 362880, 1.0 / 3628800,
-                              1.0 / 39916800, 1.0 / 479001600, 1.0 / 6227020800.0};
-    double e = c[13];
-#pragma unroll
-    for (int k = 12; k >= 0; --k) e = __builtin_fma(e, r, c[k]);
-    return __builtin_ldexp(e, -(int)n);
-}
 
 // pixels of a block: whole pixels' rays in 64 lanes, or one pixel in rounds
 __host__ __device__ inline int primary_pixels(int sub) {
