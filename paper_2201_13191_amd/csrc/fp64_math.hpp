@@ -25,6 +25,12 @@ __device__ __forceinline__ double fast_div(double n, double d) {
     return __builtin_fma(__builtin_fma(-d, q, n), r, q);
 }
 
+// the same with r = fast_rcp(d) at hand
+__device__ __forceinline__ double div_by(double n, double d, double r) {
+    const double q = n * r;
+    return __builtin_fma(__builtin_fma(-d, q, n), r, q);
+}
+
 // n / d for a constant d whose rounded reciprocal is inv
 __device__ __forceinline__ double div_const(double n, double d, double inv) {
     const double q = n * inv;
@@ -37,6 +43,13 @@ __device__ __forceinline__ double fast_rsqrt(double x) {
     const double hx = 0.5 * x;
     r = __builtin_fma(r, __builtin_fma(-hx * r, r, 0.5), r);
     return __builtin_fma(r, __builtin_fma(-hx * r, r, 0.5), r);
+}
+
+// sqrt(x), corrected once as fast_div's quotient is
+__device__ __forceinline__ double fast_sqrt(double x) {
+    const double r = fast_rsqrt(x);
+    const double g = x * r;
+    return __builtin_fma(__builtin_fma(-g, g, x), 0.5 * r, g);
 }
 
 // x^(-1/3) to an ulp or two for x in [1e-30, 1e30]: an fp32 estimate z (a few

@@ -484,6 +484,8 @@ constexpr int kPrefetch = MCX_PREFETCH;   // march steps whose voxel loads are i
 // An unclamped group reads up to kPrefetch - 1 step centres past a flight's last
 // step; with steps of at most one voxel those lie within the edge copies.
 static_assert(kPrefetch + 1 <= kEdgePad, "unclamped gathers would read past the edge copies");
+constexpr uint32_t kPdIdle = 24;  // lanes without a flight worth a round of pseudo-particles
+                                  // (12 .. 24 the same, 32 2 % and 40 9 % slower)
 constexpr int kLdsHeader = 256 + 64;   // floats: palette densities, then 256 palette ids
 
 // the value lane `src` (wave-uniform) holds, read into a scalar register
@@ -728,24 +730,34 @@ transport_kernel(const KParams p) {
         if (STATS) ++st[kStHist];
     };
 
-    // point-detector scoring (PD): the next pseudo-particle of the lane's
-    // scattering event (-1: none pending), its process, the flight in progress
-    // being a pseudo-particle's chord, and that pseudo-particle's unattenuated
-    // score and scatter bin
-    int pd_i = -1;
-    bool pd_rayl = false, pd_flight = false;
+    // Point-detector scoring (PD).  The pseudo-particles of the photons that wait
+    // at a scattering are pairs (photon, i) which any lane of the wave may take,
+    // so that a wave evaluates 64 at a time and the ones roulette removes do
+    // not hold up the others (each lane looping over its own photon's left 5.9
+    // of 64 lanes active, now 17.4; 1e6 photons, split 20, 1 keV roulette:
+    // 3.15 -> 0.92 ms).  pd_wait: the lane's photon waits at a
+    // scattering, 1 to be listed, 2 with pairs left to hand out, 3 with all of
+    // them taken (it scatters once its lane is free).  The listed photons'
+    // lanes are ranked, Compton events first: lane r's pd_src is the lane of
+    // rank r; pairs 0 .. pd_total - 1 are handed out in order, pd_next next.
+    // pd_flight: the lane's flight is a pseudo-particle's chord, pd_done it has
+    // left the object; pd_x0, pd_bin: its unattenuated score and scatter bin.
+    int pd_wait = 0, pd_src = 0;
+    bool pd_rayl = false, pd_flight = false, pd_done = false;
+    uint32_t pd_next = 0, pd_total = 0, pd_compton = 0, pd_events = 0;
+    double pd_norm = 1.0;       // the waiting event's angular normalisation
     double pd_x0 = 0.0;
     uint32_t pd_bin = 0;
     const double pd_area = (double)((float)p.nu * p.pu) * (double)((float)p.nv * p.pv);
 
-    // the march of a new flight along `dir` from o, entering at tin and leaving
+    // the march of a new flight along `dir` from `org`, entering at tin and leaving
     // at tout: voxel coordinates of the first step's nominal centre, the
     // per-step increment, the step count and the last step's length
-    auto start_march = [&](const VoxelGrid &gr, const float dir[3], float tout)
+    auto start_march = [&](const VoxelGrid &gr, const float org[3], const float dir[3], float tout)
         __attribute__((always_inline)) {
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            const float pin = o[a] + dir[a] * tin;
+            const float pin = org[a] + dir[a] * tin;
             G[a] = (dir[a] * gr.inv_h) * p.step;
             c0[a] = (pin - gr.lo[a]) * gr.inv_h + 0.5f * G[a];
             q[a] = c0[a] + 0.0f * G[a];
@@ -814,15 +826,22 @@ transport_kernel(const KParams p) {
         }
     };
 
-    // point detector, eq. (3)-(5): the pseudo-particle pd_i of the photon's
-    // n_int-th scattering at o (incoming direction d, energy e) picks a uniform
-    // point on the panel from its own Philox block (counter photon id, n_int,
-    // pd_i + 1; the photon's draws use counters ending in 0) and scores
+    // Point detector, eq. (3)-(5): pseudo-particle i of a photon's n-th scattering
+    // (at v.o, incoming direction v.d, energy v.e) picks a uniform point on the
+    // panel from its own Philox block (counter photon id, n, i + 1; the photon's
+    // draws use counters ending in 0) and scores
     // eta(E') p(lambda) cos(gamma) A / (2 pi R^2 split) exp(-tau), tau the
-    // optical depth at E' from o to the object's exit.  Roulette below
-    // pd_rr (section II-C-1).  Returns true when the chord's march started;
-    // false when the pseudo-particle needs none (killed, below 1 keV, or
-    // scored at once because it leaves the object without a step).
+    // optical depth at E' from v.o to the object's exit.  Roulette below
+    // pd_rr (section II-C-1).  Starts the chord's march on this lane, unless the
+    // pseudo-particle needs none (killed, below 1 keV, or scored at once
+    // because it leaves the object without a step).
+    struct PdEvent {
+        uint32_t pid_lo, pid_hi, n;
+        float o[3], d[3], e;
+        int mat;
+        double norm;
+        bool rayl;
+    };
     auto pd_score = [&](double tau_chord) __attribute__((always_inline)) {
         const double x = pd_x0 * exp_neg(tau_chord * kTick);
         const long long t = (long long)__builtin_rint(x * 1048576.0);
@@ -831,137 +850,183 @@ transport_kernel(const KParams p) {
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (STATS) ++st[kStPdScores];
     };
-    auto pd_start = [&]() __attribute__((always_inline)) -> bool {
+    auto pd_start = [&](const PdEvent &v, uint32_t i) __attribute__((always_inline)) {
         const ProjFrame &F = p.F;
-        if (p.pd_mode == 2 && pd_rayl) {
+        const uint64_t id = ((uint64_t)v.pid_hi << 32) | v.pid_lo;
+        float om[3], e2 = v.e;
+        double x0, u_rr;
+        int iu, iv;
+        if (p.pd_mode == 2 && v.rayl) {
             // mixed estimator: a Rayleigh pseudo-particle draws its direction
             // from the Rayleigh law (its own stream) and scores eta(E) / split
             // exp(-tau) where that line crosses the panel
             PseudoStream ps;
-            ps.reset_pseudo(pid, p.key0, p.key1, (uint32_t)(BIND ? n_coll : n_int),
-                            (uint32_t)pd_i);
-            const float ct = sample_rayleigh(ps, e, p.rayl_b[mat]);
+            ps.reset_pseudo(id, p.key0, p.key1, v.n, i);
+            const float ct = sample_rayleigh(ps, v.e, p.rayl_b[v.mat]);
             double sphi, cphi;
             sincos_2pi(6.283185307179586 * (double)ps.u(), sphi, cphi);
-            float om[3] = {d[0], d[1], d[2]};
+#pragma unroll
+            for (int a = 0; a < 3; ++a) om[a] = v.d[a];
             rotate_direction(om[0], om[1], om[2], ct, sqrtf(fmaxf(0.0f, 1.0f - ct * ct)),
                              (float)cphi, (float)sphi);
-            int iu, iv;
-            if (!panel_hit(p, F, o, om, iu, iv)) return false;
-            double x0 = (double)grid_lerp(p.eta, p.J, e) / (double)p.pd_split;
-            const double u_rr = (double)ps.u();
-            if (p.pd_rr > 0.0 && x0 < p.pd_rr) {
-                if (u_rr < x0 / p.pd_rr) {
-                    x0 = p.pd_rr;
-                } else {
-                    if (STATS) ++st[kStPdKilled];
-                    return false;
-                }
-            }
-            pd_x0 = x0;
-            pd_bin = (uint32_t)(bin_of(iv, p.inv_bv) * p.snu + bin_of(iu, p.inv_bu));
-            float tout;
-            if (!box_entry(p.G, o, om, tin, tout)) {
-                pd_score(0.0);
-                return false;
-            }
-            if (tab_e != e) {
-                refresh_mu(e, p.G);
-                tab_e = e;
-            }
-            start_march(p.G, om, tout);
-            ts = __builtin_inf();
-            pd_flight = true;
-            if (STATS) ++st[kStFlights];
-            return true;
-        }
-        const uint4 w = philox4x32_10(make_uint4((uint32_t)pid, (uint32_t)(pid >> 32),
-                                                 (uint32_t)(BIND ? n_coll : n_int),
-                                                 (uint32_t)pd_i + 1u),
-                                      p.key0, p.key1);
-        const float fu = unit_float(w.x) * (float)p.nu;
-        const float fv = unit_float(w.y) * (float)p.nv;
-        int iu = (int)fu, iv = (int)fv;
-        iu = iu > p.nu - 1 ? p.nu - 1 : iu;
-        iv = iv > p.nv - 1 ? p.nv - 1 : iv;
-        const float uu = fu * p.pu - F.hu, vv = fv * p.pv - F.hv;
-        float dq[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) dq[a] = ((F.D[a] + uu * F.eu[a]) + vv * F.ev[a]) - o[a];
-        const double r2 =
-            ((double)dq[0] * dq[0] + (double)dq[1] * dq[1]) + (double)dq[2] * dq[2];
-        const double dist = sqrt(r2);
-        double lam =
-            (((double)d[0] * dq[0] + (double)d[1] * dq[1]) + (double)d[2] * dq[2]) / dist;
-        lam = lam > 1.0 ? 1.0 : (lam < -1.0 ? -1.0 : lam);
-        const double cg =
-            (((double)F.ax[0] * dq[0] + (double)F.ax[1] * dq[1]) + (double)F.ax[2] * dq[2]) /
-            dist;
-        float e2;
-        double pdf;
-        if (!pd_rayl) {
-            // eq. (4): Klein-Nishina per unit cosine, at the Compton energy
-            const double alpha = (double)e / 510.99895;
-            const double ratio = 1.0 + alpha * (1.0 - lam);
-            const double r = 1.0 / ratio;
-            e2 = (float)((double)e / ratio);
-            pdf = r * r * ((r + ratio) - (1.0 - lam * lam)) / kn_norm(p, alpha);
-            if (BIND && (p.phys & 1u)) {
-                // the law's deficit under S/Z is the null collisions' share
-                const double t = (double)e / 12.398419843320026;
-                pdf *= incoh_sf(p.rayl_b[mat], t * t, 1.0 - lam);
-            }
-            if (BIND && (p.phys & 2u)) {
-                // the broadened energy towards the point, from the
-                // pseudo-particle's own stream
-                PseudoStream ps;
-                ps.reset_pseudo(pid, p.key0, p.key1, (uint32_t)n_coll, (uint32_t)pd_i);
-                e2 = (float)((double)e * sample_doppler(ps, p.pz_scale[mat], ratio, 1.0 - lam));
-            }
+            if (!panel_hit(p, F, v.o, om, iu, iv)) return;
+            x0 = (double)grid_lerp(p.eta, p.J, v.e) / (double)p.pd_split;
+            u_rr = (double)ps.u();
         } else {
-            // eq. (5): (1 + lambda^2) F^2 per unit cosine, energy unchanged
-            const double t = (double)e / 12.398419843320026;
-            const double V = t * t;
-            const double b = p.rayl_b[mat];
-            const double wv = 1.0 + b * ((1.0 - lam) * 0.5 * V);
-            e2 = e;
-            pdf = (1.0 + lam * lam) / (((wv * wv) * wv) * wv) / (2.0 * coherent_shape(p, b * V));
+            const uint4 w = philox4x32_10(make_uint4(v.pid_lo, v.pid_hi, v.n, i + 1u), p.key0,
+                                          p.key1);
+            const float fu = unit_float(w.x) * (float)p.nu;
+            const float fv = unit_float(w.y) * (float)p.nv;
+            iu = (int)fu;
+            iv = (int)fv;
+            iu = iu > p.nu - 1 ? p.nu - 1 : iu;
+            iv = iv > p.nv - 1 ? p.nv - 1 : iv;
+            u_rr = (double)unit_float(w.z);
+            const float uu = fu * p.pu - F.hu, vv = fv * p.pv - F.hv;
+            float dq[3];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) dq[a] = ((F.D[a] + uu * F.eu[a]) + vv * F.ev[a]) - v.o[a];
+            const double r2 =
+                ((double)dq[0] * dq[0] + (double)dq[1] * dq[1]) + (double)dq[2] * dq[2];
+            const double dist = fast_sqrt(r2), rd = fast_rcp(dist);
+            double lam = div_by(
+                ((double)v.d[0] * dq[0] + (double)v.d[1] * dq[1]) + (double)v.d[2] * dq[2], dist, rd);
+            lam = lam > 1.0 ? 1.0 : (lam < -1.0 ? -1.0 : lam);
+            const double cg = div_by(
+                ((double)F.ax[0] * dq[0] + (double)F.ax[1] * dq[1]) + (double)F.ax[2] * dq[2], dist,
+                rd);
+            double pdf;
+            if (!v.rayl) {
+                // eq. (4): Klein-Nishina per unit cosine, at the Compton energy
+                const double alpha = div_const((double)v.e, 510.99895, 1.0 / 510.99895);
+                const double ratio = 1.0 + alpha * (1.0 - lam);
+                const double rr = fast_rcp(ratio);
+                const double r = div_by(1.0, ratio, rr);
+                e2 = (float)div_by((double)v.e, ratio, rr);
+                pdf = fast_div(r * r * ((r + ratio) - (1.0 - lam * lam)), v.norm);
+                if (BIND && (p.phys & 1u)) {
+                    // the law's deficit under S/Z is the null collisions' share
+                    const double t = div_const((double)v.e, 12.398419843320026,
+                                               1.0 / 12.398419843320026);
+                    pdf *= incoh_sf(p.rayl_b[v.mat], t * t, 1.0 - lam);
+                }
+                if (BIND && (p.phys & 2u)) {
+                    // the broadened energy towards the point, from the
+                    // pseudo-particle's own stream
+                    PseudoStream ps;
+                    ps.reset_pseudo(id, p.key0, p.key1, v.n, i);
+                    e2 = (float)((double)v.e *
+                                 sample_doppler(ps, p.pz_scale[v.mat], ratio, 1.0 - lam));
+                }
+            } else {
+                // eq. (5): (1 + lambda^2) F^2 per unit cosine, energy unchanged
+                const double t = div_const((double)v.e, 12.398419843320026,
+                                           1.0 / 12.398419843320026);
+                const double V = t * t;
+                const double wv = 1.0 + p.rayl_b[v.mat] * ((1.0 - lam) * 0.5 * V);
+                pdf = fast_div((1.0 + lam * lam) / (((wv * wv) * wv) * wv), v.norm);
+            }
+            if (e2 < 1.0f) return;            // such a photon would be killed
+            const double eta = (double)grid_lerp(p.eta, p.J, e2);
+            x0 = fast_div(((eta * pdf) * cg) * pd_area,
+                          (6.283185307179586 * r2) * (double)p.pd_split);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) om[a] = (float)div_by((double)dq[a], dist, rd);
         }
-        if (e2 < 1.0f) return false;      // such a photon would be killed
-        const double eta = (double)grid_lerp(p.eta, p.J, e2);
-        double x0 = (((eta * pdf) * cg) * pd_area) /
-                    ((6.283185307179586 * r2) * (double)p.pd_split);
         if (p.pd_rr > 0.0 && x0 < p.pd_rr) {
-            if ((double)unit_float(w.z) < x0 / p.pd_rr) {
+            if (u_rr < x0 / p.pd_rr) {
                 x0 = p.pd_rr;
             } else {
                 if (STATS) ++st[kStPdKilled];
-                return false;
+                return;
             }
         }
         pd_x0 = x0;
         pd_bin = (uint32_t)(bin_of(iv, p.inv_bv) * p.snu + bin_of(iu, p.inv_bu));
-        float om[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) om[a] = (float)((double)dq[a] / dist);
         float tout;
-        if (!box_entry(p.G, o, om, tin, tout)) {
+        if (!box_entry(p.G, v.o, om, tin, tout)) {
             pd_score(0.0);
-            return false;
+            return;
         }
         if (tab_e != e2) {
             refresh_mu(e2, p.G);
             tab_e = e2;
         }
-        start_march(p.G, om, tout);
+        start_march(p.G, v.o, om, tout);
         ts = __builtin_inf();
         pd_flight = true;
         if (STATS) ++st[kStFlights];
-        return true;
+    };
+    // value x of lane src (every lane of the wave takes part)
+    auto from = [&](int src, uint32_t x) __attribute__((always_inline)) {
+        return (uint32_t)__builtin_amdgcn_ds_bpermute(src << 2, (int)x);
+    };
+    auto from_f = [&](int src, float x) __attribute__((always_inline)) {
+        return __uint_as_float(from(src, __float_as_uint(x)));
+    };
+    // Hands out pairs to the lanes without a flight, a round at a time, until
+    // fewer than pd_idle of them are left (or no pairs).  pd_idle is at most the
+    // event batch: the march gives way once that many lanes wait, and a round
+    // must then find enough of them.
+    const uint32_t pd_idle = (uint32_t)p.event_batch < kPdIdle ? (uint32_t)p.event_batch : kPdIdle;
+    auto pd_pairs = [&]() __attribute__((always_inline)) {
+        for (;;) {
+            if (pd_next >= pd_total) {
+                // every pair of the list is taken: the photons that wait make a new one
+                if (pd_wait == 2) pd_wait = 3;
+                const unsigned long long mc = __ballot(pd_wait == 1 && !pd_rayl);
+                const unsigned long long mr = __ballot(pd_wait == 1 && pd_rayl);
+                pd_compton = (uint32_t)__popcll(mc);
+                pd_events = pd_compton + (uint32_t)__popcll(mr);
+                pd_next = 0;
+                pd_total = pd_events * (uint32_t)p.pd_split;
+                if (pd_events == 0u) return;
+                // ranks: Compton events, Rayleigh events, then the other lanes
+                const unsigned long long below = (1ull << lane) - 1ull;
+                const bool c = (mc >> lane) & 1ull, r = (mr >> lane) & 1ull;
+                const uint32_t rank =
+                    c ? (uint32_t)__popcll(mc & below)
+                    : r ? pd_compton + (uint32_t)__popcll(mr & below)
+                        : pd_events + (uint32_t)__popcll(~(mc | mr) & below);
+                pd_src = __builtin_amdgcn_ds_permute((int)(rank << 2), lane);
+                if (c || r) pd_wait = 2;
+            }
+            const unsigned long long idle = __ballot(!flying);
+            const uint32_t n_idle = (uint32_t)__popcll(idle);
+            if (n_idle < pd_idle) return;
+            const uint32_t left = pd_total - pd_next;
+            const uint32_t rank = (uint32_t)__popcll(idle & ((1ull << lane) - 1ull));
+            const bool mine = !flying && rank < left;
+            // pair t: Compton events first, pseudo-particle t / events of event
+            // t % events (t is below 2^16, so the fp32 quotient truncates right)
+            uint32_t t = mine ? pd_next + rank : 0u;
+            const uint32_t in_compton = pd_compton * (uint32_t)p.pd_split;
+            const bool ray = t >= in_compton;
+            const uint32_t n = ray ? pd_events - pd_compton : pd_compton;
+            t = ray ? t - in_compton : t;
+            const uint32_t i = (uint32_t)(((float)t + 0.5f) * __builtin_amdgcn_rcpf((float)n));
+            const uint32_t r = t - i * n + (ray ? pd_compton : 0u);
+            const int src = (int)from((int)r, (uint32_t)pd_src);
+            PdEvent v;
+            v.pid_lo = from(src, (uint32_t)pid);
+            v.pid_hi = from(src, (uint32_t)(pid >> 32));
+            v.n = from(src, (uint32_t)(BIND ? n_coll : n_int));
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                v.o[a] = from_f(src, o[a]);
+                v.d[a] = from_f(src, d[a]);
+            }
+            v.e = from_f(src, e);
+            v.mat = (int)from(src, (uint32_t)mat);
+            v.norm = __hiloint2double((int)from(src, (uint32_t)__double2hiint(pd_norm)),
+                                      (int)from(src, (uint32_t)__double2loint(pd_norm)));
+            v.rayl = ray;
+            if (mine) pd_start(v, i);
+            pd_next += n_idle < left ? n_idle : left;
+        }
     };
 
-    // pending: 1 interaction, 2 reaches the panel plane (left or missed the box),
-    // 3 a pseudo-particle's chord left the object
+    // pending: 1 interaction, 2 reaches the panel plane (left or missed the box)
     int event = 0;
     for (;;) {
         int end = -1;
@@ -976,38 +1041,38 @@ transport_kernel(const KParams p) {
                     scatter(kind == 1, end);
             }
         } else {
-            // with the point detector a scattering event first scores its
+            // with the point detector a scattering event first hands out its
             // pseudo-particles (each one's chord marched like a flight, with
-            // tau* infinite), and the photon scatters after the last one
-            bool do_scatter = false, rayl = false;
+            // tau* infinite), and the photon scatters after the last one is
+            // taken and its own lane is free
             if (event == 1) {
                 event = 0;
                 const int kind = interaction_type();
                 if (kind == 0) {
                     end = 3;
-                } else if (n_int + 1 < kMaxScatterings) {
-                    pd_i = 0;
-                    pd_rayl = kind == 1;
                 } else {
-                    do_scatter = true;      // the scattered photon is not transported
-                    rayl = kind == 1;
+                    pd_rayl = kind == 1;
+                    // (at the cap the scattered photon is not transported)
+                    pd_wait = n_int + 1 < kMaxScatterings ? 1 : 3;
+                    if (!pd_rayl) {
+                        pd_norm = kn_norm(p, div_const((double)e, 510.99895, 1.0 / 510.99895));
+                    } else if (p.pd_mode != 2) {
+                        const double t = div_const((double)e, 12.398419843320026,
+                                                   1.0 / 12.398419843320026);
+                        pd_norm = 2.0 * coherent_shape(p, p.rayl_b[mat] * (t * t));
+                    }
                 }
             }
-            if (pd_i >= 0 && !flying) {
-                if (event == 3) {
-                    event = 0;
-                    pd_flight = false;
-                    pd_score(tau);
-                    ++pd_i;
-                }
-                while (pd_i < p.pd_split && !pd_start()) ++pd_i;
-                if (pd_i >= p.pd_split) {
-                    pd_i = -1;
-                    do_scatter = true;
-                    rayl = pd_rayl;
-                }
+            if (pd_done) {
+                pd_done = false;
+                pd_flight = false;
+                pd_score(tau);
             }
-            if (do_scatter) scatter(rayl, end);
+            pd_pairs();
+            if (pd_wait == 3 && !flying) {
+                pd_wait = 0;
+                scatter(pd_rayl, end);
+            }
         }
         // ---- 2. panel crossings
         with_job(event == 2, [&](const ProjFrame &F, unsigned long long *prim,
@@ -1067,7 +1132,9 @@ transport_kernel(const KParams p) {
             // when the reservation runs short.  Reserved ids are always used up
             // (also after a cancellation, which only stops new reservations),
             // so the photons a launch runs are the prefix [0, counter).
-            const unsigned long long dead = __ballot(!alive);
+            // (a lane that marches another photon's chord is not free)
+            const bool vacant = !alive && (!PD || !flying);
+            const unsigned long long dead = __ballot(vacant);
             const unsigned nd = (unsigned)__popcll(dead);
             const uint64_t avail = res_end - res_next;
             uint64_t cb = 0, ce = 0;
@@ -1082,7 +1149,7 @@ transport_kernel(const KParams p) {
                     ce = p.n - base < p.chunk ? p.n : base + p.chunk;
                 }
             }
-            if (!alive) {
+            if (vacant) {
                 const uint64_t rank = (uint64_t)__popcll(dead & ((1ull << lane) - 1ull));
                 const bool kept = rank < avail;
                 if (kept || rank - avail < ce - cb)
@@ -1137,7 +1204,7 @@ transport_kernel(const KParams p) {
                 }
             }
         }
-        if (!__any(alive)) break;
+        if (!__any(alive || (PD && flying))) break;
 
         // ---- 3b. new directions of born and scattered photons, with one
         //          azimuth evaluation for both
@@ -1160,7 +1227,7 @@ transport_kernel(const KParams p) {
 
         // ---- 4. start flights (new photons and scattered ones); the LDS tables
         //         are rebuilt first if the energy changed since the last flight
-        with_grid(alive && !flying && event == 0, [&](const VoxelGrid &gr) __attribute__((always_inline)) {
+        with_grid(alive && !flying && event == 0 && (!PD || pd_wait == 0), [&](const VoxelGrid &gr) __attribute__((always_inline)) {
             float tout;
             if (box_entry(gr, o, d, tin, tout)) {
                 if (tab_e != e) {
@@ -1168,7 +1235,7 @@ transport_kernel(const KParams p) {
                     tab_e = e;
                 }
                 ts = (double)(float)neg_log(unit_float((uint32_t)ts)) * kTicks;
-                start_march(gr, d, tout);
+                start_march(gr, o, d, tout);
                 if (STATS) ++st[kStFlights];
             } else {
                 event = 2;
@@ -1190,7 +1257,10 @@ transport_kernel(const KParams p) {
         auto march = [&](auto each_object) __attribute__((always_inline)) {
         for (;;) {
             if (!__any(flying)) break;
-            if (__popcll(__ballot(alive && !flying)) >= (unsigned)p.event_batch) break;
+            // (with pairs to hand out, every lane without a flight waits for one)
+            if (__popcll(__ballot((alive || (PD && pd_next < pd_total)) && !flying)) >=
+                (unsigned)p.event_batch)
+                break;
             if (!flying) continue;
             each_object([&](const VoxelGrid &gl) __attribute__((always_inline)) {
             const bool lane_pal = BATCH ? gl.layout == kPaletteLane : MODE == kPaletteLane;
@@ -1390,7 +1460,7 @@ transport_kernel(const KParams p) {
                     r = r > 1.0 ? 1.0 : r;
                     tau = tau + __builtin_rint(inc_last * r);
                     k = nsteps;
-                    event = 3;
+                    pd_done = true;
                     flying = false;
                 }
             } else if (k >= nsteps) {
