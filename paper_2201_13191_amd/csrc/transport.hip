@@ -484,6 +484,10 @@ constexpr int kPrefetch = MCX_PREFETCH;   // march steps whose voxel loads are i
 // An unclamped group reads up to kPrefetch - 1 step centres past a flight's last
 // step; with steps of at most one voxel those lie within the edge copies.
 static_assert(kPrefetch + 1 <= kEdgePad, "unclamped gathers would read past the edge copies");
+// Lanes that wait for an interaction before a pass samples them, of the 44 that
+// end a march: 12 (256^3: 3.42 -> 3.37 ms, batch 5.94 -> 5.85; 18 and 24 slower), 16
+// with the longer samplers of the binding effects (0.773 -> 0.72 ms; 12: 0.727).
+constexpr int kInteract = 12, kInteractBind = 16;
 constexpr uint32_t kPdIdle = 24;  // lanes without a flight worth a round of pseudo-particles
                                   // (12 .. 24 the same, 32 2 % and 40 9 % slower)
 constexpr int kLdsHeader = 256 + 64;   // floats: palette densities, then 256 palette ids
@@ -664,6 +668,7 @@ transport_kernel(const KParams p) {
     float c0[3], q[3], G[3], ig[3];
     float tin = 0.0f, last = 0.0f;
     double tau = 0.0, ts = 0.0;
+    double hit_inc = 0.0;     // full increment of the step that met the event
     uint32_t k = 0, nsteps = 0;
     uint32_t cellw = 0;   // uniform-cell word at the centre of step k (0: none known)
     float tab_e = -1.0f;  // energy of the lane's LDS attenuation tables (-1: none yet)
@@ -676,6 +681,7 @@ transport_kernel(const KParams p) {
     float &dir_ct = last;
     uint32_t &phi_w = nsteps;
     int n_int = 0, mat = 0;
+    int event = 0;      // pending: 1 interaction, 2 reaches the panel plane (left or missed the box)
     int n_coll = 0;     // scatterings and null collisions: point-detector counters
     unsigned long long st[kStCount] = {};
     uint32_t h_steps = 0;
@@ -786,6 +792,58 @@ transport_kernel(const KParams p) {
         }
         return xs < a + b ? 1 : 2;
     };
+    // The point where the optical depth reaches tau*, for a lane whose march met
+    // it (record_hit): once per event pass, so that its division and search are
+    // not paid for by every group of the march in which some lane's flight ends.
+    auto locate_hit = [&](const VoxelGrid &gr) __attribute__((always_inline)) {
+        double inc = hit_inc;
+        const bool run = (cellw >> 8) != 0u;
+        float len = p.step;
+        uint32_t j = 0;
+        bool left = false;
+        if (run) {
+            // the first step of the run whose end reaches tau*: an fp32
+            // estimate, made exact by the fp64 checks (the run's end does)
+            const float est = (float)(ts - tau) * __builtin_amdgcn_rcpf((float)inc);
+            j = (uint32_t)fminf(fmaxf(ceilf(est) - 1.0f, 0.0f), (float)(nsteps - 1u - k));
+            while (j > 0u && tau + (double)j * inc >= ts) --j;
+            while (tau + (double)(j + 1u) * inc < ts) ++j;
+        } else if (k + 1u == nsteps) {
+            // the last step is shorter: its increment is scaled, and the photon
+            // may leave the object instead
+            double r = (double)last / (double)p.step;
+            r = r > 1.0 ? 1.0 : r;
+            inc = __builtin_rint(inc * r);
+            len = last;
+            left = !(tau + inc >= ts);
+        }
+        // (each variable is assigned on one path: stores to different ones on
+        // two paths would be merged and keep the variables in scratch memory)
+        if (DEBUG) h_steps += run ? j + 1u : 0u;
+        if (STATS) {
+            st[kStSteps] += run ? j + 1u : 0u;
+            st[kStSkipped] += run ? j + 1u : 0u;
+        }
+        tau = tau + (double)j * inc;
+        k += j;
+        event = left ? 2 : 1;
+        // the point in step k
+        const float si = (float)k * p.step + (float)(fast_div(ts - tau, inc) * (double)len);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float pin = o[a] + d[a] * tin;
+            o[a] = left ? o[a] : pin + d[a] * si;
+        }
+        // the material of palette entry c: the object's palette (staged in LDS
+        // for a single palette object), or, for a generic object, the table of
+        // the values of its uniform cells
+        const uint32_t c = cellw & 255u;
+        const int lay = BATCH ? gr.layout : MODE;
+        mat = (lay == kGeneric && !run) ? (int)c
+              : (BATCH || lay == kGeneric) ? (int)dev(gr.pal_id)[c]
+                                           : (int)s_pal_id[c];
+    };
+
     // the photon scatters: polar angle by the process's sampler, then the
     // azimuth's and the next flight's draws; cut-offs end the history
     auto scatter = [&](bool rayleigh, int &end) __attribute__((always_inline)) {
@@ -1026,13 +1084,24 @@ transport_kernel(const KParams p) {
         }
     };
 
-    // pending: 1 interaction, 2 reaches the panel plane (left or missed the box)
-    int event = 0;
     for (;;) {
         int end = -1;
         // ---- 1. interactions of lanes whose flight ended inside the object
+        //         A pass takes them once kInteract lanes wait for one (a pass costs the
+        //         samplers' whole length for however few): until then they wait while
+        //         births and crossings are handled, unless nothing else flies or no
+        //         photons are left to take.  (Never more than the event batch: the
+        //         march gives way to that many waiting lanes, so a pass must then
+        //         take them.)
+        constexpr int kEnough = BIND ? kInteractBind : kInteract;
+        const bool interact =
+            PD || exhausted || !__any(flying) ||
+            __popcll(__ballot(event == 1)) >= (p.event_batch < kEnough ? p.event_batch : kEnough);
+        with_grid(event == 1 && interact, [&](const VoxelGrid &gr) __attribute__((always_inline)) {
+            locate_hit(gr);
+        });
         if constexpr (!PD) {
-            if (event == 1) {
+            if (event == 1 && interact) {
                 event = 0;
                 const int kind = interaction_type();
                 if (kind == 0)
@@ -1254,36 +1323,34 @@ transport_kernel(const KParams p) {
         static_assert(kPrefetch % 4 == 0, "groups hold whole anchor periods");
         // march(each_object): the loop of groups; each_object(f) runs one
         // group f for the flying lanes with their object's descriptor
+        // with no photons left to take, a wave goes on to the events once three
+        // quarters of its photons wait (a small launch is as long as its longest
+        // history, which would wait for each of the others' flights: 1e5 photons
+        // 194 -> 187 us)
+        unsigned batch = (unsigned)p.event_batch;
+        if (!PD && exhausted) {
+            const unsigned most = ((unsigned)__popcll(__ballot(alive)) * 3u + 3u) / 4u;
+            batch = most < batch ? most : batch;
+        }
         auto march = [&](auto each_object) __attribute__((always_inline)) {
         for (;;) {
             if (!__any(flying)) break;
             // (with pairs to hand out, every lane without a flight waits for one)
-            if (__popcll(__ballot((alive || (PD && pd_next < pd_total)) && !flying)) >=
-                (unsigned)p.event_batch)
+            if ((unsigned)__popcll(__ballot((alive || (PD && pd_next < pd_total)) && !flying)) >=
+                batch)
                 break;
             if (!flying) continue;
             each_object([&](const VoxelGrid &gl) __attribute__((always_inline)) {
             const bool lane_pal = BATCH ? gl.layout == kPaletteLane : MODE == kPaletteLane;
             const bool skips = gl.cells != nullptr;
             const int lay = BATCH ? gl.layout : MODE;
-            // the material of palette entry c: the object's palette (staged in
-            // LDS for a single palette object), or, for a generic object, the
-            // table of the values of its uniform cells
-            auto pal_material = [&](uint32_t c) __attribute__((always_inline)) -> int {
-                return (BATCH || lay == kGeneric) ? (int)dev(gl.pal_id)[c] : (int)s_pal_id[c];
-            };
-            // c: the voxel's code (generic: its material), or, with run = true,
-            // the palette entry of the uniform region the run went through
-            auto interact = [&](uint32_t c, double inc, float len, bool run)
-                __attribute__((always_inline)) {
-                // the point where the optical depth reaches tau* inside step k
-                const float si = (float)k * p.step + (float)((ts - tau) / inc * (double)len);
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    const float pin = o[a] + d[a] * tin;
-                    o[a] = pin + d[a] * si;
-                }
-                mat = (lay == kGeneric && !run) ? (int)c : pal_material(c);
+            // the lane met its event at step k, whose full increment is inc (or, with
+            // run, within the run of such steps ahead of it); c: the voxel's code
+            // (generic: its material) or the uniform region's palette entry.  The
+            // event pass finds the point (locate_hit).
+            auto record_hit = [&](uint32_t c, double inc, bool run) __attribute__((always_inline)) {
+                hit_inc = inc;
+                cellw = run ? c | 256u : c;
                 event = 1;
                 flying = false;
             };
@@ -1296,19 +1363,21 @@ transport_kernel(const KParams p) {
             if (skips && (cellw >> 8) != 0u && k + 1u < nsteps) {
                 const uint32_t cell = cellw;
                 cellw = 0u;
-                const uint32_t cc[3] = {voxel_index(q[0], gl.cmax[0]) >> kCellLog,
-                                        voxel_index(q[1], gl.cmax[1]) >> kCellLog,
-                                        voxel_index(q[2], gl.cmax[2]) >> kCellLog};
-                const int r = (int)(cell >> 8);
+                // steps along axis a until the cube's face (a margin inside it): with
+                // the cell's low corner c, (c + 2 - q) / G + (4 r - 2 - margin) / |G|
+                // for cells of 4 voxels.  Along an axis without motion this is
+                // NaN, which bounds nothing.
+                constexpr float kCell = (float)(1 << kCellLog);
+                const float reach = (float)(cell >> 8) * kCell - (0.5f * kCell + kSkipMargin);
                 float n = 4194304.0f;
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
-                    const bool neg = (__float_as_uint(G[a]) >> 31) != 0u;
-                    const float bound =
-                        neg ? (float)(((int)cc[a] - r + 1) * (1 << kCellLog)) + kSkipMargin
-                            : (float)(((int)cc[a] + r) * (1 << kCellLog)) - kSkipMargin;
-                    n = fminf(n, fmaxf((bound - q[a]) * ig[a], 0.0f));
+                    const float low =
+                        (float)(voxel_index(q[a], gl.cmax[a]) & ~((1u << kCellLog) - 1u));
+                    const float far = __builtin_fmaf(reach, __builtin_fabsf(ig[a]), 0.5f * kCell * ig[a]);
+                    n = fminf(n, __builtin_fmaf(low - q[a], ig[a], far));
                 }
+                n = fmaxf(n, 0.0f);
                 uint32_t cnt = (uint32_t)n;
                 const uint32_t avail = nsteps - 1u - k;
                 cnt = (cnt < avail ? cnt : avail) & ~3u;
@@ -1329,21 +1398,7 @@ transport_kernel(const KParams p) {
                     }
                     const double tn = tau + (double)cnt * inc;
                     if (tn >= ts) {
-                        // the first step of the run whose end reaches tau*:
-                        // an fp32 estimate, made exact by the fp64 checks
-                        const float est = (float)(ts - tau) * __builtin_amdgcn_rcpf((float)inc);
-                        uint32_t j = (uint32_t)fminf(fmaxf(ceilf(est) - 1.0f, 0.0f),
-                                                     (float)(cnt - 1u));
-                        while (j > 0u && tau + (double)j * inc >= ts) --j;
-                        while (tau + (double)(j + 1u) * inc < ts) ++j;
-                        if (DEBUG) h_steps += j + 1u;
-                        if (STATS) {
-                            st[kStSteps] += j + 1u;
-                            st[kStSkipped] += j + 1u;
-                        }
-                        tau = tau + (double)j * inc;
-                        k += j;
-                        interact(c, inc, p.step, true);
+                        record_hit(c, inc, true);
                     } else {
                         if (DEBUG) h_steps += cnt;
                         if (STATS) {
@@ -1468,21 +1523,7 @@ transport_kernel(const KParams p) {
                 event = 2;
                 flying = false;
             } else if (hit) {
-                if (k + 1u == nsteps) {
-                    // the last step is shorter: its increment is scaled, and the
-                    // photon may leave the object instead
-                    double r = (double)last / (double)p.step;
-                    r = r > 1.0 ? 1.0 : r;
-                    const double inc_l = __builtin_rint(inc_hit * r);
-                    if (tau + inc_l >= ts) {
-                        interact(code_hit, inc_l, last, false);
-                    } else {
-                        event = 2;
-                        flying = false;
-                    }
-                } else {
-                    interact(code_hit, inc_hit, p.step, false);
-                }
+                record_hit(code_hit, inc_hit, false);
             }
             });
         }
