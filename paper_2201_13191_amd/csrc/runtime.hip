@@ -391,7 +391,7 @@ VoxelGrid grid_of(const mc_ctx *c, const Phantom &ph) {
     G.layout = phantom_layout(c, ph);
     G.nx = ph.nx; G.ny = ph.ny; G.nz = ph.nz;
     G.nbx = ph.nbx; G.nby = ph.nby;
-    G.ry = (uint32_t)ph.nbx * kBrick - 32u;
+    G.ry = (uint32_t)ph.nbx * kBrick - 64u;
     G.rz = (uint32_t)ph.nbx * ph.nby * kBrick - 128u;
     G.unclamped = ph.edge_pad >= kEdgePad && c->g.step_mm <= ph.h;
     G.cmax[0] = (float)(ph.nx - 1);
@@ -637,9 +637,14 @@ mc_status build_phantom(mc_ctx *c, const uint8_t *ids, const float *rho, int nx,
     }
     const size_t nv = (size_t)nx * ny * nz;
     const size_t padded = (size_t)nbx * nby * nbz * kBrick;
-    if (padded >= (size_t)1 << 31) return fail(c, MC_E_INVALID_ARG, "phantom too large (2^31 voxels)");
-    // the kernel multiplies brick strides in 24 bits
-    if ((size_t)nbx * nby * kBrick - kBrick >= ((size_t)1 << 24))
+    // Limits of an object, in units of 4 voxels along y and z: below 2^31 such
+    // voxels (this layout's offsets, whose rounding at most doubles them, then
+    // fit 32 bits), and an x-y slab below 16 MiB (the kernel multiplies brick
+    // strides in 24 bits, and a brick is flatter than that slab).
+    const size_t slab4 = (size_t)((nx + 7) / 8) * ((ny + 3) / 4) * kBrick;
+    if (slab4 * ((nz + 3) / 4) >= (size_t)1 << 31)
+        return fail(c, MC_E_INVALID_ARG, "phantom too large (2^31 voxels)");
+    if (slab4 - kBrick >= ((size_t)1 << 24))
         return fail(c, MC_E_INVALID_ARG, "phantom too large (an x-y slab of bricks above 16 MiB)");
     // validate and collect the distinct (id, density) pairs, first appearance first
     int max_id = 0;

@@ -507,15 +507,15 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
 }
 
 // byte offset of voxel (ix, iy, iz) in the bricked arrays,
-//   (iz>>2)*slab + (iy>>2)*row + (ix>>3)*128 + (iz&3)*32 + (iy&3)*8 + (ix&7),
-// regrouped as ix + 120*(ix>>3) + 8*iy + (row-32)*(iy>>2) + 32*iz + (slab-128)*(iz>>2)
+//   (iz>>1)*slab + (iy>>3)*row + (ix>>3)*128 + (iz&1)*64 + (iy&7)*8 + (ix&7),
+// regrouped as ix + 120*(ix>>3) + 8*iy + (row-64)*(iy>>3) + 64*iz + (slab-128)*(iz>>1)
 // so that each axis costs one shift and one 24-bit multiply-add (the runtime
-// keeps row-32 and slab-128 below 2^24)
+// keeps row-64 and slab-128 below 2^24)
 __device__ __forceinline__ uint32_t brick_offset(const VoxelGrid &p, uint32_t ix, uint32_t iy,
                                                  uint32_t iz) {
     uint32_t o = __umul24(ix >> 3, 120u) + ix;
-    o += __umul24(iy >> 2, p.ry) + (iy << 3);
-    o += __umul24(iz >> 2, p.rz) + (iz << 5);
+    o += __umul24(iy >> 3, p.ry) + (iy << 3);
+    o += __umul24(iz >> 1, p.rz) + (iz << 6);
     return o;
 }
 
