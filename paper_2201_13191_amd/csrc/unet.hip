@@ -20,6 +20,7 @@
 // gradient and the flipped, transposed weights.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "nn_params.hpp"
@@ -38,6 +39,16 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
     const uint32_t u = __float_as_uint(f);
     if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);
     return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
+}
+
+// Blocks go to the 8 XCDs in turn, each with its own L2.  The rank of a block
+// among all when those of one XCD come first: consecutive ranks run on one XCD,
+// so that blocks with common inputs (neighbouring rows, the tiles of one pixel
+// range) find them in its L2.
+constexpr uint32_t kXcds = 8;
+__device__ __forceinline__ uint32_t xcd_rank(uint32_t block, uint32_t blocks) {
+    const uint32_t xcd = block % kXcds, each = blocks / kXcds, more = blocks % kXcds;
+    return xcd * each + min(xcd, more) + block / kXcds;
 }
 
 #ifndef MCX_CONV_DEPTH
@@ -648,87 +659,182 @@ __global__ void __launch_bounds__(256) wgrad_kernel(const WgradArgs a) {
     }
 }
 
-// dW[co][tap][ci] = sum over splits in order (fp32), optionally + bias grads
-// The same weight gradient for images whose width is a multiple of 16, with
-// all nine taps of a 32(co) x 32(ci) tile in one block: a wave takes 16-pixel
-// slices of one image row, stages the slice of dY and the three input rows
-// around it, 18 pixels wide (zeros outside the image), channel-major in its
-// own LDS, and issues the nine taps' products from there.  Split ranges are
-// whole slices; partial tiles are laid out as wgrad_kernel's.
-constexpr int kWgStride = 24;   // bf16 per staged channel row (16-byte aligned rows)
+// The same weight gradient for images whose width is a multiple of 16, all nine
+// taps of a 32(co) x 32(ci) tile in one block.  A slice is 16 pixels of one row
+// (one k-step of the matrix product); a wave walks down a 16-pixel column of
+// slices, so that every input row is staged once and meets the three
+// output-gradient rows whose fragments it keeps in registers: 9 products per
+// staged row, from three shifted reads.  Both operands need eight pixels of one
+// channel per lane while memory holds channels together: the rows go to LDS as
+// they are and are read transposed (ds_read_b64_tr_b16: lane t of 16 gives the
+// address of row t / 4, columns 4 (t % 4) .. +4, and receives column t of the
+// four rows), where transposing 2-byte stores and reads of single elements
+// took most of the time.  The next rows' loads are in flight meanwhile.  A
+// block's eight waves take consecutive shares of its split's slices and add
+// their tiles in LDS in a fixed order; the host sizes the splits for one block
+// a compute unit, since every split's partial tile is written and read again
+// (8 x 64^2, 192 -> 64 channels: 71 us with 86 splits, now 18.5 + 5 with 21).
+typedef __attribute__((__vector_size__(4 * sizeof(short)))) short bf16x4;
+typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
-__global__ void __launch_bounds__(256) wgrad9_kernel(const WgradArgs a) {
-    __shared__ __align__(16) uint16_t s_dy[4][32][kWgStride];      // [wave][co][pixel]
-    __shared__ __align__(16) uint16_t s_x[4][3][32][kWgStride];    // [wave][row][ci][pixel + 1]
-    __shared__ float s_acc[4][32][33];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int co0 = blockIdx.x * 32, ci0 = blockIdx.y * 32, split = blockIdx.z;
-    const int npix = a.n * a.h * a.w_;
-    const int per = (((npix + a.splits - 1) / a.splits) + 15) & ~15;
-    const int p_lo = min(npix, split * per), p_hi = min(npix, p_lo + per);
+// eight pixels of this lane's channel from staged rows (32 channels each): pixels
+// 8 (lane / 32) + 0 .. 7 past `row0`, channel lane % 32
+__device__ __forceinline__ bf16x8 read_pixels(const uint16_t *row0, int lane) {
+    const int t = lane & 15;
+    const uint16_t *p = row0 + (8 * (lane >> 5) + (t >> 2)) * 32 + 16 * ((lane >> 4) & 1) + 4 * (t & 3);
+    const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bf16x4 *)p);
+    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bf16x4 *)(p + 4 * 32));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+#ifndef MCX_WG_DEPTH
+#define MCX_WG_DEPTH 3
+#endif
+constexpr int kWgDepth = MCX_WG_DEPTH;   // staged rows in flight
+
+constexpr int kWgWaves = 8;       // of a block
+
+__global__ void __launch_bounds__(64 * kWgWaves, 2) wgrad9_kernel(const WgradArgs a, int splits) {
+    // per wave: an input row slice of 18 pixels and an output-gradient slice of
+    // 16, 32 channels each; then the waves' tiles of four taps
+    constexpr int kStage = (18 + 16) * 32;
+    __shared__ __align__(16) union {
+        uint16_t stage[kWgWaves][kStage];
+        float sum[4][kWgWaves][16][64];        // [tap][wave][register][lane]
+    } lds;
+    // (the wave's number is made uniform, so that its strips' rows, pointers and
+    // branches are scalar)
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // the tiles of one split, which read the same pixels, on one XCD
+    const uint32_t tiles_co = ((uint32_t)a.cout + 31) / 32, tiles_ci = ((uint32_t)a.cin + 31) / 32;
+    const uint32_t rank = xcd_rank(blockIdx.x, gridDim.x);
+    const int split = (int)(rank / (tiles_co * tiles_ci));
+    const uint32_t tile = rank - (uint32_t)split * (tiles_co * tiles_ci);
+    const int co0 = (int)(tile / tiles_ci) * 32, ci0 = (int)(tile % tiles_ci) * 32;
+    uint16_t *s_x = lds.stage[wave], *s_dy = lds.stage[wave] + 18 * 32;
+    // slices in the order (image, column, row), rows fastest: fewer than 2^26
+    const uint32_t cols = (uint32_t)a.w_ >> 4, slices = (uint32_t)a.n * cols * (uint32_t)a.h;
+    const uint32_t share = (uint32_t)split * kWgWaves + wave, shares = (uint32_t)splits * kWgWaves;
+    uint32_t at = (uint32_t)((uint64_t)slices * share / shares);
+    const uint32_t end = (uint32_t)((uint64_t)slices * (share + 1) / shares);
     f32x16 acc[9];
 #pragma unroll
     for (int t = 0; t < 9; ++t)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
-    const int kh = lane >> 5, lr = lane & 31;
-    auto put8 = [](uint16_t *dst, int stride, uint4 v) __attribute__((always_inline)) {
-        const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) dst[e * stride] = (uint16_t)(w4[e >> 1] >> (16 * (e & 1)));
-    };
-    for (int p0 = p_lo + wave * 16; p0 < p_hi; p0 += 64) {
-        const int row = p0 / a.w_;            // n * h + y of the slice's row
-        const int xx0 = p0 - row * a.w_;
-        const int yy = row % a.h;
-        {
-            // dY: pixel p0 + (lane & 15), channels co0 + 8 * (lane >> 4) .. +8
-            const int pl = lane & 15, c = co0 + (lane >> 4) * 8;
-            uint4 v = make_uint4(0u, 0u, 0u, 0u);
-            if (c < a.cout) v = *(const uint4 *)(a.dy + (size_t)(p0 + pl) * a.ldy + a.yoff + c);
-            put8(&s_dy[wave][c - co0][pl], kWgStride, v);
-        }
-        // input rows yy - 1 .. yy + 1, pixels xx0 - 1 .. xx0 + 16, 8 channels per item
-        for (int t = lane; t < 3 * 18 * 4; t += 64) {
-            const int cq = t & 3, q = t >> 2;
-            const int r = q / 18, px = q - r * 18;
-            const int y2 = yy + r - 1, x2 = xx0 + px - 1, c = ci0 + cq * 8;
-            uint4 v = make_uint4(0u, 0u, 0u, 0u);
-            if (y2 >= 0 && y2 < a.h && x2 >= 0 && x2 < a.w_ && c < a.cin)
-                v = *(const uint4 *)(a.x + ((size_t)(row + r - 1) * a.w_ + x2) * a.ldx + a.xoff + c);
-            put8(&s_x[wave][r][cq * 8][px], kWgStride, v);
-        }
-        wave_sync();
-        const bf16x8 av = *(const bf16x8 *)&s_dy[wave][lr][kh * 8];
-#pragma unroll
-        for (int r = 0; r < 3; ++r)
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                bf16x8 bv;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) bv[e] = (short)s_x[wave][r][lr][kh * 8 + k + e];
-                acc[3 * r + k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[3 * r + k],
-                                                                         0, 0, 0);
+    const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+    const uint4 none = make_uint4(0u, 0u, 0u, 0u);
+    // staged item m: pixel m / 4, channels 8 (m % 4) .. +8; lane's items of the
+    // input row are lane and (first 8 lanes) 64 + lane
+    const int pl = lane >> 2, cq = (lane & 3) * 8;
+    const bool ci_ok = ci0 + cq < a.cin, co_ok = co0 + cq < a.cout;
+    const uint32_t vx0 = (uint32_t)(pl * a.ldx + cq), vx1 = vx0 + 16u * (uint32_t)a.ldx;
+    const uint32_t vy = (uint32_t)(pl * a.ldy + cq);
+    while (at < end) {
+        const uint32_t col = at / (uint32_t)a.h;
+        const int y0 = (int)(at - col * (uint32_t)a.h);
+        const int y1 = (int)min((uint32_t)a.h, (uint32_t)y0 + (end - at));
+        at += (uint32_t)(y1 - y0);
+        const uint32_t img = col / cols;
+        const int x0 = (int)(col - img * cols) * 16;
+        // pixel x0 - 1 (input) and x0 (output gradient) of the image's first row
+        const int64_t pix = (int64_t)img * a.h * a.w_ + x0;
+        const uint16_t *xcol = a.x + (pix - 1) * a.ldx + a.xoff + ci0;
+        const uint16_t *ycol = a.dy + pix * a.ldy + a.yoff + co0;
+        const int64_t xrow = (int64_t)a.w_ * a.ldx, yrow = (int64_t)a.w_ * a.ldy;
+        const bool left_ok = ci_ok && x0 + pl >= 1;                       // pixel x0 - 1 + pl
+        const bool right_ok = ci_ok && lane < 8 && x0 + 15 + pl < a.w_;   // pixel x0 + 15 + pl
+        // input row j and output-gradient row j + 1 (zeros outside the image and
+        // the strip), kWgDepth rows in flight
+        struct Rows {
+            uint4 x0, x1, y;
+        };
+        auto load = [&](int j) __attribute__((always_inline)) -> Rows {
+            Rows r{none, none, none};
+            if (j >= 0 && j < a.h && j <= y1) {
+                const uint16_t *p = xcol + j * xrow;
+                if (left_ok) r.x0 = *(const uint4 *)(p + vx0);
+                if (right_ok) r.x1 = *(const uint4 *)(p + vx1);
             }
-        wave_sync();      // the next slice overwrites the staging
-    }
-    // per tap: the 4 waves' tiles added in LDS in a fixed order, then this
-    // split's partial written
+            if (j + 1 < y1 && co_ok) r.y = *(const uint4 *)(ycol + (j + 1) * yrow + vy);
+            return r;
+        };
+        bf16x8 a0, a1 = zero, a2 = zero;       // output-gradient rows j - 1, j, j + 1
+        Rows ring[kWgDepth];
 #pragma unroll
-    for (int t = 0; t < 9; ++t) {
+        for (int q = 0; q < kWgDepth; ++q) ring[q] = load(y0 - 1 + q);
+        for (int j0 = y0 - 1; j0 <= y1; j0 += kWgDepth) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s_acc[wave][8 * (r >> 2) + 4 * kh + (r & 3)][lr] = acc[t][r];
-        __syncthreads();
-        for (int i = threadIdx.x; i < 32 * 32; i += 256) {
-            const int rr = i >> 5, col = i & 31;
-            const float v = ((s_acc[0][rr][col] + s_acc[1][rr][col]) + s_acc[2][rr][col]) +
-                            s_acc[3][rr][col];
-            const int co = co0 + rr, ci = ci0 + col;
-            if (co < a.cout && ci < a.cin)
-                a.partial[(((size_t)split * 9 + t) * a.cout + co) * a.cin + ci] = v;
+            for (int q = 0; q < kWgDepth; ++q) {
+                // (rows past the strip's end are zeros, and change nothing)
+                *(uint4 *)(s_x + lane * 8) = ring[q].x0;
+                if (lane < 8) *(uint4 *)(s_x + (64 + lane) * 8) = ring[q].x1;
+                *(uint4 *)(s_dy + lane * 8) = ring[q].y;
+                ring[q] = load(j0 + q + kWgDepth);
+                wave_sync();
+                a0 = a1;
+                a1 = a2;
+                a2 = read_pixels(s_dy, lane);
+                bf16x8 b[3];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) b[k] = read_pixels(s_x + k * 32, lane);
+                wave_sync();      // the next row overwrites the staging
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    acc[6 + k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b[k], acc[6 + k], 0, 0, 0);
+                    acc[3 + k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b[k], acc[3 + k], 0, 0, 0);
+                    acc[k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, b[k], acc[k], 0, 0, 0);
+                }
+            }
         }
-        __syncthreads();
     }
+    // four taps at a time, two waves each add the block's tiles of one of them in
+    // a fixed order and write half of this split's partial
+    const int kh = lane >> 5, lr = lane & 31;
+#pragma unroll
+    for (int t0 = 0; t0 < 9; t0 += 4) {
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (t0 + q < 9)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) lds.sum[q][wave][r][lane] = acc[t0 + q][r];
+        __syncthreads();
+        const int q = wave >> 1, t = t0 + q, ci = ci0 + lr;
+        if (t < 9 && ci < a.cin) {
+#pragma unroll
+            for (int h = 0; h < 8; ++h) {
+                const int r = 8 * (wave & 1) + h;
+                float v = lds.sum[q][0][r][lane];
+#pragma unroll
+                for (int w = 1; w < kWgWaves; ++w) v += lds.sum[q][w][r][lane];
+                const int co = co0 + 8 * (r >> 2) + 4 * kh + (r & 3);
+                if (co < a.cout) a.partial[(((size_t)split * 9 + t) * a.cout + co) * a.cin + ci] = v;
+            }
+        }
+    }
+}
+
+// dw[co][tap][ci] from the splits' partial tiles [split][tap][co][ci], summed in
+// order
+__global__ void __launch_bounds__(256) wgrad_sum_kernel(const float *partial, int splits, int cout,
+                                                        int cin, float *dw) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int n = 9 * cout * cin;
+    if (i >= n) return;
+    const int ci = i % cin, co = (i / cin) % cout, tap = i / (cin * cout);
+    float s = 0.0f;
+    int k = 0;
+    for (; k + 8 <= splits; k += 8) {
+        float v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = partial[(size_t)(k + q) * n + i];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) s += v[q];
+    }
+    for (; k < splits; ++k) s += partial[(size_t)k * n + i];
+    dw[((size_t)co * 9 + tap) * cin + ci] = s;
 }
 
 // Sum of the splits' partial tiles in a fixed order, in two levels: groups of
@@ -1040,10 +1146,26 @@ hipError_t nn_conv3x3(const ConvArgs &a, hipStream_t s) {
     return conv_launch<2, 2>(a, (a.cout + 63) / 64, s);
 }
 
+#ifndef MCX_WG_BLOCKS
+#define MCX_WG_BLOCKS 256
+#endif
+constexpr int kWgBlocks = MCX_WG_BLOCKS;
+
 hipError_t nn_wgrad(const WgradArgs &a, float *tmp, float *dw, hipStream_t s) {
     if (a.w_ % 16 == 0 && (a.ldy | a.yoff) % 8 == 0 && ((uintptr_t)a.dy & 15) == 0) {
-        const dim3 grid((a.cout + 31) / 32, (a.cin + 31) / 32, a.splits);
-        hipLaunchKernelGGL(wgrad9_kernel, grid, dim3(256), 0, s, a);
+        // one block a compute unit (a few more would run after the others: 252 blocks
+        // 18.5 us, 264 30.6, 516 of half as many waves 34), at least 4 slices a wave, and
+        // never more splits than the caller's workspace holds
+        const int tiles_co = (a.cout + 31) / 32, tiles_ci = (a.cin + 31) / 32;
+        const int64_t slices = (int64_t)a.n * a.h * (a.w_ / 16);
+    const int64_t want = std::max<int64_t>(1, kWgBlocks / (tiles_co * tiles_ci));
+        const int splits = (int)std::max<int64_t>(
+            1, std::min<int64_t>(a.splits, std::min<int64_t>(want, slices / (4 * kWgWaves))));
+        hipLaunchKernelGGL(wgrad9_kernel, dim3(tiles_co * tiles_ci * splits), dim3(64 * kWgWaves), 0, s, a,
+                           splits);
+        hipLaunchKernelGGL(wgrad_sum_kernel, dim3(blocks_for((int64_t)9 * a.cout * a.cin)),
+                           dim3(256), 0, s, (const float *)a.partial, splits, a.cout, a.cin, dw);
+        return hipGetLastError();
     } else {
         const dim3 grid((a.cout + 31) / 32, 9 * ((a.cin + 31) / 32), a.splits);
         hipLaunchKernelGGL(wgrad_kernel, grid, dim3(256), 0, s, a);
