@@ -44,7 +44,8 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
 // Blocks go to the 8 XCDs in turn, each with its own L2.  The rank of a block
 // among all when those of one XCD come first: consecutive ranks run on one XCD,
 // so that blocks with common inputs (neighbouring rows, the tiles of one pixel
-// range) find them in its L2.
+// range) find them in its L2 (a forward pass of the network on 8 maps of 128^2,
+// whose convolutions read every row in three blocks: 318 -> 300 us).
 constexpr uint32_t kXcds = 8;
 __device__ __forceinline__ uint32_t xcd_rank(uint32_t block, uint32_t blocks) {
     const uint32_t xcd = block % kXcds, each = blocks / kXcds, more = blocks % kXcds;
@@ -198,7 +199,7 @@ __global__ void __launch_bounds__(256) conv3x3_kernel(const ConvArgs a) {
     const int tile = wave / KS, ks = wave - tile * KS;
     const int hw = a.h * a.w_;
     const int npix = a.n * hw;
-    const int px0 = (blockIdx.x * TPB + tile) * (32 * WM);
+    const int px0 = ((int)xcd_rank(blockIdx.x, gridDim.x) * TPB + tile) * (32 * WM);
     const int co0 = blockIdx.y * (32 * WN);
     const bool live = px0 < npix;       // no early return: the block meets at a barrier
     const int kh = lane >> 5;           // which 8-channel half of the 16-k slice
@@ -353,7 +354,7 @@ __global__ void __launch_bounds__(256) conv3x3_lds_kernel(const ConvArgs a) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int kh = lane >> 5, lr = lane & 31;
     const int npix = a.n * a.h * a.w_;
-    const int px0 = (blockIdx.x * 4 + wave) * (32 * WM);
+    const int px0 = ((int)xcd_rank(blockIdx.x, gridDim.x) * 4 + wave) * (32 * WM);
     const int co0 = blockIdx.y * (32 * WN);
     const bool live = px0 < npix;       // no early return: the block meets at barriers
     const int row = live ? px0 / a.w_ : 0;   // n * h + y of the wave's pixels
@@ -463,7 +464,7 @@ __global__ void __launch_bounds__(256) conv3x3_lds_split_kernel(const ConvArgs a
     const int kh = lane >> 5, lr = lane & 31;
     uint16_t *in = (uint16_t *)s_dyn + wave * kLdsInElems;
     const int npix = a.n * a.h * a.w_;
-    const int px0 = (blockIdx.x * TPB + tile) * (32 * WM);
+    const int px0 = ((int)xcd_rank(blockIdx.x, gridDim.x) * TPB + tile) * (32 * WM);
     const int co0 = blockIdx.y * (32 * WN);
     const bool live = px0 < npix;       // no early return: the block meets at barriers
     const bool wide = a.w_ >= TPX;
