@@ -95,13 +95,14 @@ __global__ void fdk_filter_row_kernel(const float *proj, FdkGeom g, float *q) {
 // 32 * WR rows and 16 * NT * WC column pairs, each of its 4 waves 32 rows by
 // 16 * NT pairs of both halves, so every weighted value is made once for rows
 // of up to 512 pixels and read from LDS 2 * NT times (17.2 -> 1.76 ms at
-// 360 x 512^2, 188 -> 20 us at 180 x 128^2); the reduction runs over
+// 360 x 512^2, 188 -> 20 us at 180 x 128^2; 1.2 ms with the registers held to
+// two blocks a compute unit); the reduction runs over
 // chunks of 32 column pairs, whose weighted inputs and the NT * WC * 16 + 32
 // taps that the chunk meets are staged in LDS.  Sums are fp64 throughout.
 constexpr int kFltPairs = 32;      // column pairs per chunk
 
 template <int WR, int WC, int NT>
-__global__ void __launch_bounds__(256) fdk_filter_kernel(const float *proj, FdkGeom g,
+__global__ void __launch_bounds__(256, 2) fdk_filter_kernel(const float *proj, FdkGeom g,
                                                          int rows, float *q) {
     static_assert(WR * WC == 4, "four waves");
     constexpr int TR = 32 * WR;              // rows of a block
