@@ -38,7 +38,7 @@ hipError_t launch_batch(const KParams &p, int max_lane_palette, int grid, int bl
                         hipStream_t stream);
 int batch_blocks_per_cu(const KParams &p, int max_lane_palette, int block, bool stats);
 hipError_t launch_clear(unsigned long long *a, size_t na, unsigned long long *b, size_t nb,
-                        hipStream_t stream);
+                        unsigned long long *c, size_t nc, hipStream_t stream);
 hipError_t launch_primary(const KParams &p, int sub, const double *bin_w, const float *bin_mu,
                           int n_bins, float *out, hipStream_t stream);
 hipError_t launch_interp_angles(const float *sim, int n_sim, uint64_t n_pix, float *full,
@@ -508,10 +508,14 @@ void launch_shape(mc_ctx *c, const KParams &p, int layout, bool stats, int &grid
     grid = (int)std::max<uint64_t>(1, std::min(full, need));
 }
 
-mc_status run(mc_ctx *c, KParams &p, hipStream_t s, bool debug) {
-    if (p.n == 0) return MC_OK;
+// Clears the launch's photon counter and, with np > 0, the images p.prim[np] and
+// p.scat[ns], then runs the photons.
+mc_status run(mc_ctx *c, KParams &p, hipStream_t s, bool debug, size_t np = 0, size_t ns = 0) {
+    if (p.n == 0 && np == 0) return MC_OK;
     if (debug) p.pd_split = 0;   // per-history records are the same with either estimator
-    HIP_TRY(c, hipMemsetAsync(p.counter, 0, sizeof(unsigned long long), s));
+    const hipError_t cleared = launch_clear(p.prim, np, p.scat, ns, p.counter, 1, s);
+    if (cleared != hipSuccess) return hip_fail(c, cleared, "clear launch");
+    if (p.n == 0) return MC_OK;
     const bool stats = c->stats_on && !debug;
     const int layout = p.G.layout;
     int grid, block;
@@ -1096,12 +1100,10 @@ mc_status mc_project_async(mc_ctx *c, float beta, uint64_t n, uint64_t seed, int
     KParams p;
     rc = prepare(c, beta, 0, n, seed, p);
     if (rc) return rc;
-    hipStream_t s = (hipStream_t)stream;
-    HIP_TRY(c, hipMemsetAsync(d_prim, 0, (size_t)c->g.nu * c->g.nv * sizeof(int64_t), s));
-    HIP_TRY(c, hipMemsetAsync(d_scat, 0, (size_t)c->g.snu * c->g.snv * sizeof(int64_t), s));
     p.prim = (unsigned long long *)d_prim;
     p.scat = (unsigned long long *)d_scat;
-    return run(c, p, s, false);
+    return run(c, p, (hipStream_t)stream, false, (size_t)c->g.nu * c->g.nv,
+               (size_t)c->g.snu * c->g.snv);
 }
 
 mc_status mc_march_probe_async(mc_ctx *c, float beta, uint64_t n_rays, uint64_t seed,
@@ -1119,7 +1121,8 @@ mc_status mc_march_probe_async(mc_ctx *c, float beta, uint64_t n_rays, uint64_t 
     p.event_batch = refill_batch;
     p.stats = nullptr;
     hipStream_t s = (hipStream_t)stream;
-    HIP_TRY(c, hipMemsetAsync(p.counter, 0, sizeof(unsigned long long), s));
+    const hipError_t cleared = launch_clear(nullptr, 0, nullptr, 0, p.counter, 1, s);
+    if (cleared != hipSuccess) return hip_fail(c, cleared, "clear launch");
     // the probe's own occupancy (it uses no LDS) unless the caller fixed a shape
     const int block = c->block > 0 ? c->block : 256;
     const int bpc = c->blocks_per_cu > 0 ? c->blocks_per_cu
@@ -1213,7 +1216,7 @@ mc_status mc_project_batch(mc_ctx *c, const mc_job *jobs, int n_jobs, int64_t *d
 
     if (!(flags & MC_BATCH_GRAPH)) {
         hipError_t e = launch_clear((unsigned long long *)d_out, out_elems, p.job_counters,
-                                    (size_t)n_jobs, s);
+                                    (size_t)n_jobs, nullptr, 0, s);
         if (e == hipSuccess) e = launch_batch(p, b.max_lane_pal, grid, block, stats, s);
         if (e != hipSuccess) return hip_fail(c, e, "batch launch");
         HIP_TRY(c, hipEventRecord(c->batch_done, s));
@@ -1237,7 +1240,7 @@ mc_status mc_project_batch(mc_ctx *c, const mc_job *jobs, int n_jobs, int64_t *d
         HIP_TRY(c, hipStreamSynchronize(s));
         HIP_TRY(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
         hipError_t e = launch_clear((unsigned long long *)d_out, out_elems, p.job_counters,
-                                    (size_t)n_jobs, c->stream);
+                                    (size_t)n_jobs, nullptr, 0, c->stream);
         if (e == hipSuccess) e = launch_batch(p, b.max_lane_pal, grid, block, stats, c->stream);
         hipGraph_t gr = nullptr;
         const hipError_t e2 = hipStreamEndCapture(c->stream, &gr);
@@ -1276,7 +1279,7 @@ mc_status mc_project_batch_static(mc_ctx *c, const mc_job *jobs, int n_jobs, int
     bool stats;
     batch_params(c, b, db, n_jobs, p, grid, block, stats);
     hipError_t e = launch_clear((unsigned long long *)d_out, out_elems, p.job_counters,
-                                (size_t)n_jobs, s);
+                                (size_t)n_jobs, nullptr, 0, s);
     if (e == hipSuccess) e = launch_batch(p, b.max_lane_pal, grid, block, stats, s);
     if (e != hipSuccess) return hip_fail(c, e, "static batch launch");
     return MC_OK;

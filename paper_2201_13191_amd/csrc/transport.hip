@@ -1959,22 +1959,28 @@ hipError_t launch_interp_angles(const float *sim, int n_sim, uint64_t n_pix, flo
     return hipGetLastError();
 }
 
-// zero a batch's images and counters: a plain fill kernel, so the batch can
-// be captured in a graph without memset nodes
-__global__ void clear_kernel(unsigned long long *a, size_t na, unsigned long long *b, size_t nb) {
+// Zeroes images and photon counters in one launch (a projection's two images and
+// its counter took three fills, some 4 us each): a plain fill kernel, so that
+// it can be captured in a graph without memset nodes.
+__global__ void clear_kernel(unsigned long long *a, size_t na, unsigned long long *b, size_t nb,
+                             unsigned long long *c, size_t nc) {
     const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < na; i += stride) a[i] = 0ull;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nb; i += stride) b[i] = 0ull;
+    const size_t first = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (size_t i = first; i < na; i += stride) a[i] = 0ull;
+    for (size_t i = first; i < nb; i += stride) b[i] = 0ull;
+    for (size_t i = first; i < nc; i += stride) c[i] = 0ull;
 }
 
 hipError_t launch_clear(unsigned long long *a, size_t na, unsigned long long *b, size_t nb,
-                        hipStream_t stream) {
-    const size_t n = na > nb ? na : nb;
+                        unsigned long long *c, size_t nc, hipStream_t stream) {
+    size_t n = na > nb ? na : nb;
+    n = n > nc ? n : nc;
     const int block = 256;
     size_t grid = (n + block - 1) / block;
     if (grid > 4096) grid = 4096;
     if (grid == 0) grid = 1;
-    hipLaunchKernelGGL(clear_kernel, dim3((unsigned)grid), dim3(block), 0, stream, a, na, b, nb);
+    hipLaunchKernelGGL(clear_kernel, dim3((unsigned)grid), dim3(block), 0, stream, a, na, b, nb,
+                       c, nc);
     return hipGetLastError();
 }
 
