@@ -315,22 +315,29 @@ __global__ void __launch_bounds__(256) conv3x3_kernel(const ConvArgs a) {
 }
 
 // The same convolution for images whose width is a multiple of 64, on layers
-// with enough tiles for one wave each (2 x 32 pixels x 32*WN channels): a
-// wave's 64 output pixels lie in one image row.  The reduction runs over
-// 16-channel chunks; for each chunk every wave stages the three input rows
-// around its pixels (66 pixels wide, zeros outside the image) and the block
-// stages the nine taps' weights, pixel- and channel-major as in memory, in
-// LDS, so each input value is loaded once per chunk instead of once per tap.
-// The next chunk's loads are in flight in registers while the products of
-// the current one are issued.
+// with enough tiles for one wave each.  A block computes 4 image rows of 64
+// pixels, a wave one of them (2 x 32 pixels x 32*WN channels).  The reduction
+// runs over 16-channel chunks; for each chunk the block stages the six input
+// rows around its own (66 pixels wide, zeros outside the image) and the nine
+// taps' weights, pixel- and channel-major as in memory, in LDS, so each input
+// value is loaded once per chunk instead of once per tap, and 1.5 times in all
+// (with a window of its own per wave every row was staged three times).  The
+// next chunk's loads are in flight in registers while the products of the
+// current one are issued.
 constexpr int kLdsInPx = 66;                          // staged pixels per row
 constexpr int kLdsInElems = 3 * kLdsInPx * 16;        // one wave's rows, one chunk (bf16)
 
 template <int WN>
 constexpr int lds_w_elems() { return 9 * 32 * WN * 16; }   // the block's weights, one chunk
 
+constexpr int kLdsRows = 4;                                // output rows of a block, one a wave
+constexpr int kLdsBlockElems = (kLdsRows + 2) * kLdsInPx * 16;   // staged input, one chunk
 template <int WN>
-constexpr size_t conv_lds_bytes() { return (4 * kLdsInElems + lds_w_elems<WN>()) * 2; }
+constexpr size_t conv_lds_bytes() {
+    constexpr size_t chunk = (kLdsBlockElems + lds_w_elems<WN>()) * 2;
+    constexpr size_t epilogue = kLdsRows * 32 * kEpStride * sizeof(float);
+    return chunk > epilogue ? chunk : epilogue;
+}
 
 #ifndef MCX_CONV_LDS
 #define MCX_CONV_LDS 1
@@ -344,34 +351,35 @@ constexpr bool conv_half_tiles = MCX_CONV_HALF_TILES != 0;
 template <int WN>
 __global__ void __launch_bounds__(256) conv3x3_lds_kernel(const ConvArgs a) {
     constexpr int WM = 2;
-    constexpr int kInItems = 3 * kLdsInPx * 2;                  // 16-byte items per wave
-    constexpr int kInPer = (kInItems + 63) / 64;
-    constexpr int kWItems = 9 * 32 * WN * 2;                    // 16-byte items per block
+    constexpr int kInItems = (kLdsRows + 2) * kLdsInPx * 2;     // 16-byte items of the window
+    constexpr int kInPer = (kInItems + 255) / 256;
+    constexpr int kWItems = 9 * 32 * WN * 2;                    // and of the weights
     constexpr int kWPer = (kWItems + 255) / 256;
-    static_assert(32 * kEpStride * 4 <= kLdsInElems * 2, "epilogue staging fits a wave's rows");
     extern __shared__ __align__(16) float s_dyn[];
-    uint16_t *lds = (uint16_t *)s_dyn;
+    uint16_t *in = (uint16_t *)s_dyn, *wl = in + kLdsBlockElems;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int kh = lane >> 5, lr = lane & 31;
-    const int npix = a.n * a.h * a.w_;
-    const int px0 = ((int)xcd_rank(blockIdx.x, gridDim.x) * 4 + wave) * (32 * WM);
+    // block: (image, group of 4 rows, 64-pixel segment), segments fastest
+    const int segs = a.w_ >> 6, groups = (a.h + kLdsRows - 1) / kLdsRows;
+    const int rank = (int)xcd_rank(blockIdx.x, gridDim.x);
+    const int x0 = (rank % segs) * 64, y0 = (rank / segs) % groups * kLdsRows;
+    const int img = rank / (segs * groups);
     const int co0 = blockIdx.y * (32 * WN);
-    const bool live = px0 < npix;       // no early return: the block meets at barriers
-    const int row = live ? px0 / a.w_ : 0;   // n * h + y of the wave's pixels
-    const int x0 = px0 - row * a.w_;
-    const int yy = row % a.h;
+    const int npix = a.n * a.h * a.w_;
+    const int px0 = (img * a.h + y0 + wave) * a.w_ + x0;
+    const bool live = y0 + wave < a.h;      // no early return: the block meets at barriers
     const int kc = a.cin >> 4;
     const size_t wk = (size_t)9 * a.cin;
     uint4 rin[kInPer], rw[kWPer];
     auto load_chunk = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
         for (int m = 0; m < kInPer; ++m) {
-            const int t = lane + 64 * m;
+            const int t = threadIdx.x + 256 * m;
             const int q = t >> 1, r = q / kLdsInPx, px = q - r * kLdsInPx;
-            const int y2 = yy + r - 1, x2 = x0 + px - 1;
+            const int y2 = y0 + r - 1, x2 = x0 + px - 1;
             rin[m] = make_uint4(0u, 0u, 0u, 0u);
-            if (live && t < kInItems && y2 >= 0 && y2 < a.h && x2 >= 0 && x2 < a.w_)
-                rin[m] = *(const uint4 *)(a.x + ((size_t)(row + r - 1) * a.w_ + x2) * a.ldx +
+            if (t < kInItems && y2 >= 0 && y2 < a.h && x2 >= 0 && x2 < a.w_)
+                rin[m] = *(const uint4 *)(a.x + ((size_t)(img * a.h + y2) * a.w_ + x2) * a.ldx +
                                           a.xoff + c * 16 + (t & 1) * 8);
         }
 #pragma unroll
@@ -385,17 +393,15 @@ __global__ void __launch_bounds__(256) conv3x3_lds_kernel(const ConvArgs a) {
         }
     };
     auto store_chunk = [&]() __attribute__((always_inline)) {
-        uint16_t *in = lds + wave * kLdsInElems;
 #pragma unroll
         for (int m = 0; m < kInPer; ++m) {
-            const int t = lane + 64 * m;
-            if (t < kInItems) *(uint4 *)(in + (t >> 1) * 16 + (t & 1) * 8) = rin[m];
+            const int t = threadIdx.x + 256 * m;
+            if (t < kInItems) *(uint4 *)(in + t * 8) = rin[m];
         }
-        uint16_t *wl = lds + 4 * kLdsInElems;
 #pragma unroll
         for (int m = 0; m < kWPer; ++m) {
             const int u = threadIdx.x + 256 * m;
-            if (u < kWItems) *(uint4 *)(wl + (u >> 1) * 16 + (u & 1) * 8) = rw[m];
+            if (u < kWItems) *(uint4 *)(wl + u * 8) = rw[m];
         }
     };
     f32x16 acc[WM][WN];
@@ -408,10 +414,9 @@ __global__ void __launch_bounds__(256) conv3x3_lds_kernel(const ConvArgs a) {
     load_chunk(0);
     store_chunk();
     __syncthreads();
+    const uint16_t *mine = in + wave * kLdsInPx * 16;     // this wave's three rows
     for (int c = 0; c < kc; ++c) {
         if (c + 1 < kc) load_chunk(c + 1);
-        const uint16_t *in = lds + wave * kLdsInElems;
-        const uint16_t *wl = lds + 4 * kLdsInElems;
 #pragma unroll
         for (int r = 0; r < 3; ++r)
 #pragma unroll
@@ -419,7 +424,7 @@ __global__ void __launch_bounds__(256) conv3x3_lds_kernel(const ConvArgs a) {
                 bf16x8 av[WM], bv[WN];
 #pragma unroll
                 for (int i = 0; i < WM; ++i)
-                    av[i] = *(const bf16x8 *)(in + (r * kLdsInPx + i * 32 + lr + k) * 16 + kh * 8);
+                    av[i] = *(const bf16x8 *)(mine + (r * kLdsInPx + i * 32 + lr + k) * 16 + kh * 8);
 #pragma unroll
                 for (int j = 0; j < WN; ++j)
                     bv[j] = *(const bf16x8 *)(wl + ((3 * r + k) * 32 * WN + j * 32 + lr) * 16 +
@@ -438,8 +443,8 @@ __global__ void __launch_bounds__(256) conv3x3_lds_kernel(const ConvArgs a) {
         }
     }
     if (!live) return;
-    // the epilogue stages in this wave's rows (no longer read)
-    conv_epilogue<WM, WN>(a, acc, px0, co0, npix, (float *)(lds + wave * kLdsInElems), lane);
+    // the epilogue stages over the chunk (no longer read)
+    conv_epilogue<WM, WN>(a, acc, px0, co0, npix, s_dyn + wave * (32 * kEpStride), lane);
 }
 
 // The same staging for layers with few tiles, whose reduction is split over KS
@@ -1103,7 +1108,7 @@ static hipError_t conv_launch(const ConvArgs &a, int tiles_co, hipStream_t s) {
     const int K = 9 * (a.cin / 16);
     constexpr size_t R = WM * WN * 16 * 64 * sizeof(float);   // one partial tile
     if (WM == 2 && tiles >= 2048 && a.w_ % 64 == 0 && conv_lds_enabled) {
-        const dim3 grid((tiles_px + 3) / 4, tiles_co);
+        const dim3 grid(a.n * ((a.h + kLdsRows - 1) / kLdsRows) * (a.w_ / 64), tiles_co);
         hipLaunchKernelGGL((conv3x3_lds_kernel<WN>), grid, dim3(256), conv_lds_bytes<WN>(), s, a);
     } else if (tiles >= 2048 || K < 8) {
         const dim3 grid((tiles_px + 3) / 4, tiles_co);
