@@ -569,7 +569,8 @@ __device__ __forceinline__ uint32_t cell_word(const VoxelGrid &g, const float q[
 // follows the layout of its own job's object).  BATCH: run the job table.
 // BIND: the binding-effect samplers are compiled in (launched when p.phys is
 // non-zero); without them the default path keeps its register budget.
-template <int MODE, bool BATCH, bool STATS, bool DEBUG, bool PD, bool BIND>
+// GROUP: march steps whose voxel loads are issued together.
+template <int MODE, bool BATCH, bool STATS, bool DEBUG, bool PD, bool BIND, int GROUP>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((PD || STATS || DEBUG) ? 1 : 3)))
 transport_kernel(const KParams p) {
     static_assert(!PD || (!BATCH && !DEBUG), "point-detector scoring: single projections only");
@@ -1313,14 +1314,14 @@ transport_kernel(const KParams p) {
         // ---- 5. march until `event_batch` lanes wait for an event (or none flies).
         //         A lane whose step centre lies in a uniform region first takes
         //         the run of identical steps ahead of it at once.  Then each group
-        //         issues the voxel loads of kPrefetch consecutive steps (centres
+        //         issues the voxel loads of GROUP consecutive steps (centres
         //         re-anchored every 4 steps, added up in between) together with
         //         the uniform-cell word at the centre after the group, and
         //         consumes the steps in order without branches: the optical depth
         //         (fp64, exact) and the step index advance by selection, the step
         //         that reaches tau* is recorded, and the interaction point or the
         //         exit follows the group.
-        static_assert(kPrefetch % 4 == 0, "groups hold whole anchor periods");
+        static_assert(GROUP % 4 == 0 && GROUP <= kPrefetch, "groups hold whole anchor periods");
         // march(each_object): the loop of groups; each_object(f) runs one
         // group f for the flying lanes with their object's descriptor
         // with no photons left to take, a wave goes on to the events once three
@@ -1421,16 +1422,16 @@ transport_kernel(const KParams p) {
             // that loads them)
             float qn[3];
 #pragma unroll
-            for (int a = 0; a < 3; ++a) qn[a] = c0[a] + (kf + (float)kPrefetch) * G[a];
+            for (int a = 0; a < 3; ++a) qn[a] = c0[a] + (kf + (float)GROUP) * G[a];
             cellw = skips ? cell_word(gl, qn) : 0u;
-            uint32_t code[kPrefetch];
-            float vr[kPrefetch];
+            uint32_t code[GROUP];
+            float vr[GROUP];
             // the group's gathers; with the object's edge copies (and steps of
             // at most a voxel) the coordinates need no clamp, one copy of the
             // loop per case under a branch that is uniform across the wave
             auto gather = [&](auto index) __attribute__((always_inline)) {
 #pragma unroll
-                for (int u = 0; u < kPrefetch; ++u) {
+                for (int u = 0; u < GROUP; ++u) {
                     if (u % 4 == 0 && u > 0) {
 #pragma unroll
                         for (int a = 0; a < 3; ++a) q[a] = c0[a] + (kf + (float)u) * G[a];
@@ -1471,7 +1472,7 @@ transport_kernel(const KParams p) {
             // counting variants keep exact.
             auto consume = [&](auto inc_of) __attribute__((always_inline)) {
 #pragma unroll
-                for (int u = 0; u < kPrefetch; ++u) {
+                for (int u = 0; u < GROUP; ++u) {
                     const double inc = inc_of(u);
                     const double tn = tau + inc;
                     const bool reach = act && (tn >= ts);
@@ -1509,7 +1510,7 @@ transport_kernel(const KParams p) {
                 });
             }
             if (PD && pd_flight) {
-                if (rem <= (uint32_t)kPrefetch) {
+                if (rem <= (uint32_t)GROUP) {
                     // the chord's last step was in this group: add it, clipped
                     double r = (double)last / (double)p.step;
                     r = r > 1.0 ? 1.0 : r;
@@ -1691,15 +1692,29 @@ size_t batch_lds_bytes(const KParams &p, int max_lane_palette, int block) {
            (size_t)max_lane_palette * block * sizeof(double);
 }
 
+// Objects whose voxels fill much more than the L2s take 4 steps at a time: with
+// most steps taken in uniform runs, the tail of a group of 8 fetches lines that
+// a run would have skipped, and those fetches bound them (2e7 photons, groups
+// of 8 and 4: 512^3 codes 3.71 and 3.57 ms, 448^3 3.50 and 3.46, 384^3 3.31 and
+// 3.33, 256^3 3.00 and 3.06; ids and densities at 5 bytes a voxel, 384^3 7.73
+// and 7.08, 256^3 5.35 and 4.75, 93^3 0.71 and 0.75).  Analog single
+// projections only: the others keep one kernel each.
+constexpr int kBigGroup = 4;
+constexpr uint64_t kBigBytes = (uint64_t)64 << 20;
+static bool big_object(const KParams &p, int layout) {
+    const uint64_t voxels = (uint64_t)p.G.nx * p.G.ny * p.G.nz;
+    return voxels * (layout == kGeneric ? 5 : 1) > kBigBytes;
+}
+
 // the kernel with or without the binding-effect samplers, as p.phys asks
-template <int MODE, bool BATCH, bool STATS, bool DEBUG, bool PD>
+template <int MODE, bool BATCH, bool STATS, bool DEBUG, bool PD, int GROUP = kPrefetch>
 static void launch_k(const KParams &p, int grid, int block, size_t lds, hipStream_t stream) {
     if (p.phys)
-        hipLaunchKernelGGL((transport_kernel<MODE, BATCH, STATS, DEBUG, PD, true>), dim3(grid),
-                           dim3(block), lds, stream, p);
+        hipLaunchKernelGGL((transport_kernel<MODE, BATCH, STATS, DEBUG, PD, true, GROUP>),
+                           dim3(grid), dim3(block), lds, stream, p);
     else
-        hipLaunchKernelGGL((transport_kernel<MODE, BATCH, STATS, DEBUG, PD, false>), dim3(grid),
-                           dim3(block), lds, stream, p);
+        hipLaunchKernelGGL((transport_kernel<MODE, BATCH, STATS, DEBUG, PD, false, GROUP>),
+                           dim3(grid), dim3(block), lds, stream, p);
 }
 
 template <int MODE>
@@ -1715,6 +1730,8 @@ static hipError_t launch_mode(const KParams &p, int grid, int block, bool stats,
         launch_k<MODE, false, false, false, true>(p, grid, block, lds, stream);
     else if (stats)
         launch_k<MODE, false, true, false, false>(p, grid, block, lds, stream);
+    else if (big_object(p, MODE))
+        launch_k<MODE, false, false, false, false, kBigGroup>(p, grid, block, lds, stream);
     else
         launch_k<MODE, false, false, false, false>(p, grid, block, lds, stream);
     return hipGetLastError();
@@ -1993,21 +2010,22 @@ hipError_t launch_sample(const KParams &p, int process, int material, float e_ke
     return hipGetLastError();
 }
 
-template <int MODE, bool BATCH, bool STATS, bool PD>
+template <int MODE, bool BATCH, bool STATS, bool PD, int GROUP = kPrefetch>
 static int occ_k(int block, size_t lds, bool bind) {
     int nb = 0;
     if (bind)
         (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &nb, transport_kernel<MODE, BATCH, STATS, false, PD, true>, block, lds);
+            &nb, transport_kernel<MODE, BATCH, STATS, false, PD, true, GROUP>, block, lds);
     else
         (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &nb, transport_kernel<MODE, BATCH, STATS, false, PD, false>, block, lds);
+            &nb, transport_kernel<MODE, BATCH, STATS, false, PD, false, GROUP>, block, lds);
     return nb;
 }
 
 template <int MODE, bool BATCH>
-static int occupancy(int block, size_t lds, bool stats, bool pd, bool bind) {
+static int occupancy(int block, size_t lds, bool stats, bool pd, bool bind, bool big) {
     if constexpr (!BATCH) {
+        if (big && !stats && !pd) return occ_k<MODE, false, false, false, kBigGroup>(block, lds, bind);
         if (pd)
             return stats ? occ_k<MODE, false, true, true>(block, lds, bind)
                          : occ_k<MODE, false, false, true>(block, lds, bind);
@@ -2032,17 +2050,18 @@ int march_probe_blocks_per_cu(int layout, int block) {
 
 int transport_blocks_per_cu(const KParams &p, int layout, int block, bool stats) {
     const size_t lds = transport_lds_bytes(p, layout, block);
-    const bool pd = p.pd_split > 0, bind = p.phys != 0;
-    int nb = layout == kPaletteLane ? occupancy<kPaletteLane, false>(block, lds, stats, pd, bind)
+    const bool pd = p.pd_split > 0, bind = p.phys != 0, big = big_object(p, layout);
+    int nb = layout == kPaletteLane
+                 ? occupancy<kPaletteLane, false>(block, lds, stats, pd, bind, big)
              : layout == kPaletteShared
-                 ? occupancy<kPaletteShared, false>(block, lds, stats, pd, bind)
-                 : occupancy<kGeneric, false>(block, lds, stats, pd, bind);
+                 ? occupancy<kPaletteShared, false>(block, lds, stats, pd, bind, big)
+                 : occupancy<kGeneric, false>(block, lds, stats, pd, bind, big);
     return nb > 0 ? nb : 1;
 }
 
 int batch_blocks_per_cu(const KParams &p, int max_lane_palette, int block, bool stats) {
     const int nb = occupancy<kPaletteLane, true>(block, batch_lds_bytes(p, max_lane_palette, block),
-                                                stats, false, p.phys != 0);
+                                                stats, false, p.phys != 0, false);
     return nb > 0 ? nb : 1;
 }
 
