@@ -451,18 +451,20 @@ __global__ void __launch_bounds__(256) conv3x3_lds_kernel(const ConvArgs a) {
 // waves of a block (16-channel chunks c = ks, ks + KS, ...; partial tiles added
 // in LDS in a fixed order).  Each wave stages its chunk's input window in its
 // own LDS rows; the chunk's weights (nine taps) are loaded into registers
-// through L1/L2 at once.  The window is the tile's image rows and one more on
-// each side: for widths that are multiples of 64 one row of 66 pixels, for
+// through L1/L2 at once, for 32 channels: weights for 64 held 232 registers, two
+// waves a SIMD, and gave half as many blocks (in a forward pass on 8 maps, back to
+// back: the whole 291 -> 270 us, the first split layer 13.9 -> 9.5).  The window is
+// the tile's image rows and one more on each side: for widths that are multiples of 64 one row of 66 pixels, for
 // widths of 16 or 32 (a 64-pixel tile is 4 or 2 whole rows) the rows at their
 // full width plus the zero columns at both ends.
-template <int WM, int WN, int KS>
+template <int WM, int KS>
 __global__ void __launch_bounds__(256) conv3x3_lds_split_kernel(const ConvArgs a) {
     constexpr int TPB = 4 / KS;
     constexpr int TPX = 32 * WM;                      // pixels per tile
-    constexpr int R = WM * WN * 16;                   // floats per lane of a partial tile
+    constexpr int R = WM * 16;                        // floats per lane of a partial tile
     constexpr int kInPer = (3 * (TPX + 2) * 2 + 63) / 64;
     static_assert(3 * (TPX + 2) <= 3 * kLdsInPx, "a window fits a wave's rows");
-    static_assert(32 * kEpStride <= R * 64, "epilogue staging fits a partial tile");
+    static_assert(32 * kEpStride <= (KS - 1) * R * 64, "epilogue staging fits a tile's partials");
     extern __shared__ __align__(16) float s_dyn[];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int tile = wave / KS, ks = wave - tile * KS;
@@ -470,7 +472,7 @@ __global__ void __launch_bounds__(256) conv3x3_lds_split_kernel(const ConvArgs a
     uint16_t *in = (uint16_t *)s_dyn + wave * kLdsInElems;
     const int npix = a.n * a.h * a.w_;
     const int px0 = ((int)xcd_rank(blockIdx.x, gridDim.x) * TPB + tile) * (32 * WM);
-    const int co0 = blockIdx.y * (32 * WN);
+    const int co0 = blockIdx.y * 32;
     const bool live = px0 < npix;       // no early return: the block meets at barriers
     const bool wide = a.w_ >= TPX;
     const int nr = wide ? 1 : TPX / a.w_;             // image rows of the tile
@@ -489,13 +491,11 @@ __global__ void __launch_bounds__(256) conv3x3_lds_split_kernel(const ConvArgs a
     }
     const int kc = a.cin >> 4;
     const size_t wk = (size_t)9 * a.cin;
-    f32x16 acc[WM][WN];
+    f32x16 acc[WM][1];
 #pragma unroll
     for (int i = 0; i < WM; ++i)
 #pragma unroll
-        for (int j = 0; j < WN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+        for (int r = 0; r < 16; ++r) acc[i][0][r] = 0.0f;
     uint4 rin[kInPer];
     auto load_chunk = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
@@ -514,13 +514,11 @@ __global__ void __launch_bounds__(256) conv3x3_lds_split_kernel(const ConvArgs a
         for (int c = ks; c < kc; c += KS) {
             // the chunk's nine taps of weights, all in flight at once (one wait
             // per chunk rather than one per tap)
-            bf16x8 bw[9][WN];
+            bf16x8 bw[9];
 #pragma unroll
             for (int tap = 0; tap < 9; ++tap)
-#pragma unroll
-                for (int j = 0; j < WN; ++j)
-                    bw[tap][j] = *(const bf16x8 *)(a.w + (size_t)(co0 + j * 32 + lr) * wk +
-                                                   (size_t)tap * a.cin + c * 16 + kh * 8);
+                bw[tap] = *(const bf16x8 *)(a.w + (size_t)(co0 + lr) * wk +
+                                            (size_t)tap * a.cin + c * 16 + kh * 8);
 #pragma unroll
             for (int m = 0; m < kInPer; ++m) {
                 const int t = lane + 64 * m;
@@ -538,10 +536,8 @@ __global__ void __launch_bounds__(256) conv3x3_lds_split_kernel(const ConvArgs a
                         av[i] = *(const bf16x8 *)(in + (aoff[i] + r * wn + k) * 16 + kh * 8);
 #pragma unroll
                     for (int i = 0; i < WM; ++i)
-#pragma unroll
-                        for (int j = 0; j < WN; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                av[i], bw[3 * r + k][j], acc[i][j], 0, 0, 0);
+                        acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            av[i], bw[3 * r + k], acc[i][0], 0, 0, 0);
                 }
             wave_sync();      // the next chunk overwrites the rows
         }
@@ -554,9 +550,7 @@ __global__ void __launch_bounds__(256) conv3x3_lds_split_kernel(const ConvArgs a
 #pragma unroll
         for (int i = 0; i < WM; ++i)
 #pragma unroll
-            for (int j = 0; j < WN; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mine[((i * WN + j) * 16 + r) * 64 + lane] = acc[i][j][r];
+            for (int r = 0; r < 16; ++r) mine[(i * 16 + r) * 64 + lane] = acc[i][0][r];
     }
     __syncthreads();
     if (ks > 0) return;
@@ -566,19 +560,17 @@ __global__ void __launch_bounds__(256) conv3x3_lds_split_kernel(const ConvArgs a
 #pragma unroll
         for (int i = 0; i < WM; ++i)
 #pragma unroll
-            for (int j = 0; j < WN; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    acc[i][j][r] += base[((size_t)q * R + (i * WN + j) * 16 + r) * 64 + lane];
+            for (int r = 0; r < 16; ++r)
+                acc[i][0][r] += base[((size_t)q * R + i * 16 + r) * 64 + lane];
     }
     if (!live) return;
-    conv_epilogue<WM, WN>(a, acc, px0, co0, npix, (float *)base, lane);
+    conv_epilogue<WM, 1>(a, acc, px0, co0, npix, (float *)base, lane);
 }
 
-template <int WM, int WN, int KS>
+template <int WM, int KS>
 constexpr size_t conv_lds_split_bytes() {
     constexpr size_t rows = 4 * kLdsInElems * 2;
-    constexpr size_t parts = (size_t)(4 / KS) * (KS - 1) * WM * WN * 16 * 64 * sizeof(float);
+    constexpr size_t parts = (size_t)(4 / KS) * (KS - 1) * WM * 16 * 64 * sizeof(float);
     return rows > parts ? rows : parts;
 }
 
@@ -1116,26 +1108,28 @@ static hipError_t conv_launch(const ConvArgs &a, int tiles_co, hipStream_t s) {
                            4 * 32 * kEpStride * sizeof(float), s, a);
     } else if (WM == 2 && conv_lds_enabled &&
                (a.w_ % 64 == 0 || (a.w_ >= 16 && 64 % a.w_ == 0 && a.h % (64 / a.w_) == 0))) {
-        // the reduction split over 2 or 4 waves by 16-channel chunks
+        // the reduction split over 2 or 4 waves by 16-channel chunks, in tiles of 32
+        // channels; `tiles` counts those of 32 * WN, at which the lines were drawn
+        const int co32 = (a.cout + 31) / 32;
         if (tiles >= 1024 || a.cin < 64) {
-            const dim3 grid((tiles_px + 1) / 2, tiles_co);
-            hipLaunchKernelGGL((conv3x3_lds_split_kernel<2, WN, 2>), grid, dim3(256),
-                               (conv_lds_split_bytes<2, WN, 2>()), s, a);
+            const dim3 grid((tiles_px + 1) / 2, co32);
+            hipLaunchKernelGGL((conv3x3_lds_split_kernel<2, 2>), grid, dim3(256),
+                               (conv_lds_split_bytes<2, 2>()), s, a);
         } else {
             if constexpr (WN == 2) {
                 if (conv_half_tiles && tiles < 512 && a.cin <= 256) {
                     // the fewest tiles with short reductions: 32-pixel tiles,
                     // twice as many waves (with long reductions the weights,
                     // loaded per tile, cost more than the waves gain)
-                    const dim3 grid(2 * tiles_px, tiles_co);
-                    hipLaunchKernelGGL((conv3x3_lds_split_kernel<1, WN, 4>), grid, dim3(256),
-                                       (conv_lds_split_bytes<1, WN, 4>()), s, a);
+                    const dim3 grid(2 * tiles_px, co32);
+                    hipLaunchKernelGGL((conv3x3_lds_split_kernel<1, 4>), grid, dim3(256),
+                                       (conv_lds_split_bytes<1, 4>()), s, a);
                     return hipGetLastError();
                 }
             }
-            const dim3 grid(tiles_px, tiles_co);
-            hipLaunchKernelGGL((conv3x3_lds_split_kernel<2, WN, 4>), grid, dim3(256),
-                               (conv_lds_split_bytes<2, WN, 4>()), s, a);
+            const dim3 grid(tiles_px, co32);
+            hipLaunchKernelGGL((conv3x3_lds_split_kernel<2, 4>), grid, dim3(256),
+                               (conv_lds_split_bytes<2, 4>()), s, a);
         }
     } else if (tiles >= 1024 || K < 16) {
         const dim3 grid((tiles_px + 1) / 2, tiles_co);
