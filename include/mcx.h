@@ -421,7 +421,7 @@ mc_status mc_get_tables(mc_ctx *ctx, int *J, int *n_mat, float *pe, float *coh, 
  * AUTO: objects with <= 256 distinct (material, density) pairs are stored as
  * one-byte palette codes (per-lane attenuation table for <= 32 entries,
  * shared palette otherwise), others as material ids plus densities.  All
- * layouts are bricked (8x4x4 voxels) and give bitwise the same images. */
+ * layouts are bricked (8x8x2 voxels) and give bitwise the same images. */
 #define MC_LAYOUT_AUTO 0
 #define MC_LAYOUT_PALETTE_LANE 1
 #define MC_LAYOUT_PALETTE_SHARED 2
@@ -435,11 +435,11 @@ mc_status mc_get_layout(mc_ctx *ctx, int *layout, int *palette_size);
  * automatic): threads per block (64, 128, 192 or 256), resident blocks per
  * compute unit, and the event batch: how many of a wave's 64 lanes must be
  * waiting for an interaction or a panel crossing before the wave stops
- * marching and handles them (1 .. 64; automatic: 58).  Results never depend
+ * marching and handles them (1 .. 64; automatic: 44).  Results never depend
  * on these. */
 mc_status mc_set_launch(mc_ctx *ctx, int block, int blocks_per_cu, int event_batch);
 /* The same for mc_project_batch and mc_project_batch_static (automatic: 256
- * threads, blocks per CU from the occupancy, event batch 54).  The grid size
+ * threads, blocks per CU from the occupancy, event batch 48).  The grid size
  * (blocks per CU x compute units) sets the photons each thread takes. */
 mc_status mc_set_batch_launch(mc_ctx *ctx, int block, int blocks_per_cu, int event_batch);
 /* Objects of the context (mc_load_phantom and mc_phantom_add), their total
