@@ -574,6 +574,145 @@ constexpr size_t conv_lds_split_bytes() {
     return rows > parts ? rows : parts;
 }
 
+// The four-way split for layers of few blocks or of long enough reductions: four
+// chunks at a time, the block stages the tile's window and its 32 channels'
+// weights together, 128 bytes of each pixel and weight row by eight lanes, with
+// the next four chunks' loads in flight, where conv3x3_lds_split_kernel's waves
+// load 32 bytes of each line by themselves (an L1 access each, and the lines
+// again from the L2: 8 x 32^2, 384 -> 128 channels 24.4 -> 20.1 us, 8 x 16^2,
+// 256 -> 256 15.1 -> 11.3).  Sums are added in the same order.
+template <int WM>
+constexpr int shared_in_elems() { return (3 * (32 * WM + 2) + 1) * 16; }  // one chunk's window
+constexpr int kSharedWElems = (9 * 32 + 1) * 16;   // and its weights (16 more: the chunks' banks)
+
+template <int WM>
+__global__ void __launch_bounds__(256) conv3x3_lds_shared_kernel(const ConvArgs a) {
+    constexpr int KS = 4;
+    constexpr int TPX = 32 * WM;                      // pixels of the tile
+    constexpr int R = WM * 16;                        // floats per lane of a partial tile
+    constexpr int kIn = shared_in_elems<WM>();
+    constexpr int kInPer = (3 * (TPX + 2) * 8 + 255) / 256;     // 16-byte items a thread
+    constexpr int kWPer = 9 * 32 * 8 / 256;
+    static_assert(32 * kEpStride <= (KS - 1) * R * 64, "epilogue staging fits a tile's partials");
+    extern __shared__ __align__(16) float s_dyn[];
+    uint16_t *in = (uint16_t *)s_dyn, *wl = in + KS * kIn;
+    const int lane = threadIdx.x & 63, ks = threadIdx.x >> 6;
+    const int kh = lane >> 5, lr = lane & 31;
+    const int npix = a.n * a.h * a.w_;
+    const int px0 = (int)xcd_rank(blockIdx.x, gridDim.x) * TPX;
+    if (px0 >= npix) return;                          // the whole block
+    const int co0 = blockIdx.y * 32;
+    const bool wide = a.w_ >= TPX;
+    const int nr = wide ? 1 : TPX / a.w_;             // image rows of the tile
+    const int wn = wide ? TPX + 2 : a.w_ + 2;         // staged pixels per row
+    const int row0 = px0 / a.w_;                      // n * h + y of the tile's first row
+    const int xs = px0 - row0 * a.w_;                 // its first column (0 for whole rows)
+    const int yy0 = row0 % a.h;
+    const int items = (nr + 2) * wn * 8;              // 16-byte items of four chunks' window
+    // staged pixel of this lane's rows for tap (0, 0)
+    int aoff[WM];
+#pragma unroll
+    for (int i = 0; i < WM; ++i) {
+        const int j = i * 32 + lr;
+        const int ry = wide ? 0 : j / a.w_;
+        aoff[i] = ry * wn + (j - ry * (wide ? 0 : a.w_));
+    }
+    const int kc = a.cin >> 4;
+    const size_t wk = (size_t)9 * a.cin;
+    f32x16 acc[WM][1];
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][0][r] = 0.0f;
+    const int sub = threadIdx.x & 7, chunk = sub >> 1;     // this thread's share of each line
+    int pix[kInPer];                                       // the pixels of its items
+#pragma unroll
+    for (int m = 0; m < kInPer; ++m) {
+        const int t = threadIdx.x + 256 * m;
+        const int q = t >> 3, r = q / wn, px = q - r * wn;
+        const int y2 = yy0 + r - 1, x2 = xs + px - 1;
+        const bool ok = t < items && y2 >= 0 && y2 < a.h && x2 >= 0 && x2 < a.w_;
+        pix[m] = ok ? (row0 + r - 1) * a.w_ + x2 : -1;
+    }
+    uint4 rin[kInPer], rw[kWPer];
+    auto load_group = [&](int g) __attribute__((always_inline)) {
+        const bool have = g * KS + chunk < kc;
+#pragma unroll
+        for (int m = 0; m < kInPer; ++m) {
+            rin[m] = make_uint4(0u, 0u, 0u, 0u);
+            if (pix[m] >= 0 && have)
+                rin[m] = *(const uint4 *)(a.x + (size_t)pix[m] * a.ldx + a.xoff + g * KS * 16 +
+                                          sub * 8);
+        }
+#pragma unroll
+        for (int m = 0; m < kWPer; ++m) {
+            const int rest = (threadIdx.x >> 3) + 32 * m, col = rest & 31, tap = rest >> 5;
+            rw[m] = make_uint4(0u, 0u, 0u, 0u);
+            if (have)
+                rw[m] = *(const uint4 *)(a.w + (size_t)(co0 + col) * wk + (size_t)tap * a.cin +
+                                         g * KS * 16 + sub * 8);
+        }
+    };
+    const int groups = (kc + KS - 1) / KS;
+    load_group(0);
+    for (int g = 0; g < groups; ++g) {
+#pragma unroll
+        for (int m = 0; m < kInPer; ++m) {
+            const int t = threadIdx.x + 256 * m;
+            if (t < items) *(uint4 *)(in + chunk * kIn + (t >> 3) * 16 + (sub & 1) * 8) = rin[m];
+        }
+#pragma unroll
+        for (int m = 0; m < kWPer; ++m)
+            *(uint4 *)(wl + chunk * kSharedWElems + ((threadIdx.x >> 3) + 32 * m) * 16 +
+                       (sub & 1) * 8) = rw[m];
+        __syncthreads();
+        if (g + 1 < groups) load_group(g + 1);        // in flight during the products
+        if (g * KS + ks < kc) {
+            const uint16_t *win = in + ks * kIn, *wm = wl + ks * kSharedWElems;
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const bf16x8 bv = *(const bf16x8 *)(wm + ((3 * r + k) * 32 + lr) * 16 + kh * 8);
+#pragma unroll
+                    for (int i = 0; i < WM; ++i) {
+                        const bf16x8 av =
+                            *(const bf16x8 *)(win + (aoff[i] + r * wn + k) * 16 + kh * 8);
+                        acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[i][0], 0,
+                                                                            0, 0);
+                    }
+                }
+        }
+        __syncthreads();      // the next chunks overwrite these
+    }
+    // partial tiles of waves 1 .. 3 over the chunks (no longer read), [ks-1][register][lane]
+    if (ks > 0) {
+        float *part = s_dyn + (size_t)(ks - 1) * R * 64;
+#pragma unroll
+        for (int i = 0; i < WM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) part[(i * 16 + r) * 64 + lane] = acc[i][0][r];
+    }
+    __syncthreads();
+    if (ks > 0) return;
+#pragma unroll 1
+    for (int q = 0; q < KS - 1; ++q) {
+#pragma unroll
+        for (int i = 0; i < WM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                acc[i][0][r] += s_dyn[((size_t)q * R + i * 16 + r) * 64 + lane];
+    }
+    conv_epilogue<WM, 1>(a, acc, px0, co0, npix, s_dyn, lane);
+}
+
+template <int WM>
+constexpr size_t conv_lds_shared_bytes() {
+    constexpr size_t rows = 4 * (shared_in_elems<WM>() + kSharedWElems) * 2;
+    constexpr size_t parts = (size_t)3 * WM * 16 * 64 * sizeof(float);
+    return rows > parts ? rows : parts;
+}
+
 // ---------------------------------------------------------------------------
 // weight gradient: dW[co][tap][ci] = sum over pixels of dY[p][co] * X[p + tap][ci].
 // One block = 4 waves = a 32(co) x 32(ci) tile of one tap over a pixel range;
@@ -1111,6 +1250,18 @@ static hipError_t conv_launch(const ConvArgs &a, int tiles_co, hipStream_t s) {
         // the reduction split over 2 or 4 waves by 16-channel chunks, in tiles of 32
         // channels; `tiles` counts those of 32 * WN, at which the lines were drawn
         const int co32 = (a.cout + 31) / 32;
+        // Staged by the block in groups of 64 channels: where those come out whole
+        // (a part-filled last group costs as much as a full one: 8 x 32^2, 80 -> 128
+        // 9.8 us, 12.8 staged together), a block for each compute unit at least
+        // (fewer wait on the barriers alone: 32 blocks of 512 channels 16.0 / 16.8) and
+        // two at most, which its LDS lets run at once (4 x 32^2, 64 -> 128 6.7 / 6.3;
+        // 8 x 32^2, 384 -> 128 22.4 / 18.7; with 1024 blocks of 64 channels 9.7 / 10.5).
+        // More blocks pay with longer reductions only: from 128 channels with tiles of
+        // 32 pixels (14.0 / 13.0 at 128, 19.0 / 15.7 at 192), from 256 with 64 (128
+        // channels 19.6 / 21.5, 192 24.3 / 24.5, 256 30.0 / 28.2, 384 39.9 / 34.1).
+        auto shared = [&](long blocks, int long_cin) {
+            return a.cin % 64 == 0 && blocks >= 256 && (blocks <= 512 || a.cin >= long_cin);
+        };
         if (tiles >= 1024 || a.cin < 64) {
             const dim3 grid((tiles_px + 1) / 2, co32);
             hipLaunchKernelGGL((conv3x3_lds_split_kernel<2, 2>), grid, dim3(256),
@@ -1122,14 +1273,22 @@ static hipError_t conv_launch(const ConvArgs &a, int tiles_co, hipStream_t s) {
                     // twice as many waves (with long reductions the weights,
                     // loaded per tile, cost more than the waves gain)
                     const dim3 grid(2 * tiles_px, co32);
-                    hipLaunchKernelGGL((conv3x3_lds_split_kernel<1, 4>), grid, dim3(256),
-                                       (conv_lds_split_bytes<1, 4>()), s, a);
+                    if (shared(2L * tiles_px * co32, 128))
+                        hipLaunchKernelGGL((conv3x3_lds_shared_kernel<1>), grid, dim3(256),
+                                           conv_lds_shared_bytes<1>(), s, a);
+                    else
+                        hipLaunchKernelGGL((conv3x3_lds_split_kernel<1, 4>), grid, dim3(256),
+                                           (conv_lds_split_bytes<1, 4>()), s, a);
                     return hipGetLastError();
                 }
             }
             const dim3 grid(tiles_px, co32);
-            hipLaunchKernelGGL((conv3x3_lds_split_kernel<2, 4>), grid, dim3(256),
-                               (conv_lds_split_bytes<2, 4>()), s, a);
+            if (shared((long)tiles_px * co32, 256))
+                hipLaunchKernelGGL((conv3x3_lds_shared_kernel<2>), grid, dim3(256),
+                                   conv_lds_shared_bytes<2>(), s, a);
+            else
+                hipLaunchKernelGGL((conv3x3_lds_split_kernel<2, 4>), grid, dim3(256),
+                                   (conv_lds_split_bytes<2, 4>()), s, a);
         }
     } else if (tiles >= 1024 || K < 16) {
         const dim3 grid((tiles_px + 1) / 2, tiles_co);

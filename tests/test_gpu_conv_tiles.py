@@ -19,6 +19,21 @@ pytestmark = pytest.mark.gpu
     (1, 5, 64, 80, 70), (2, 8, 32, 64, 40), (1, 4, 16, 256, 33), (1, 1, 64, 64, 96),
     (1, 3, 64, 272, 40), (1, 4, 32, 80, 20), (1, 520, 64, 64, 48), (2, 4, 16, 288, 100)])
 def test_conv_tiles(n, h, w, cin, cout):
+    check(n, h, w, cin, cout)
+
+
+# the split reductions staged by the whole block: tiles of 32 pixels with one group of 64
+# channels and with several (wide rows, 2 whole rows of 16, more blocks than 512), tiles of
+# 64 (one group, rows of 32 and 16, the long reductions with more blocks)
+@pytest.mark.parametrize("n,h,w,cin,cout", [
+    (1, 100, 64, 64, 64), (3, 42, 32, 64, 96), (1, 260, 64, 128, 40), (17, 64, 16, 128, 33),
+    (1, 257, 64, 64, 20), (9, 60, 32, 128, 17), (17, 64, 16, 192, 32), (1, 600, 64, 256, 20),
+    (16, 16, 16, 320, 260)])
+def test_conv_shared_tiles(n, h, w, cin, cout):
+    check(n, h, w, cin, cout)
+
+
+def check(n, h, w, cin, cout):
     import torch
     print("conv tiles", n, h, w, cin, cout, flush=True)
     g = mcx.Projector(0)
