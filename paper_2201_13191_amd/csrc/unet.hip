@@ -308,7 +308,8 @@ __global__ void __launch_bounds__(256) conv3x3_kernel(const ConvArgs a) {
     if (!live) return;
     // this wave's 32 x kEpStride staging tile: in its tile's own (already
     // consumed) partial-sum region, or its own slot
-    static_assert(KS == 1 || 32 * kEpStride <= WM * WN * 16 * 64, "staging tile fits a partial");
+    static_assert(KS == 1 || 32 * kEpStride <= (KS - 1) * WM * WN * 16 * 64,
+                  "staging tile fits a tile's partials");
     float *stage = KS > 1 ? s_part + (size_t)tile * (KS - 1) * (WM * WN * 16 * 64)
                           : s_part + wave * (32 * kEpStride);
     conv_epilogue<WM, WN>(a, acc, px0, co0, npix, stage, lane);
@@ -1294,8 +1295,23 @@ static hipError_t conv_launch(const ConvArgs &a, int tiles_co, hipStream_t s) {
         const dim3 grid((tiles_px + 1) / 2, tiles_co);
         hipLaunchKernelGGL((conv3x3_kernel<WM, WN, 2>), grid, dim3(256), 2 * R, s, a);
     } else {
-        const dim3 grid(tiles_px, tiles_co);
-        hipLaunchKernelGGL((conv3x3_kernel<WM, WN, 4>), grid, dim3(256), 3 * R, s, a);
+        // The smallest tile whose blocks fit one to a compute unit: a wave's steps wait
+        // on its loads in turn, and fewer loads a step wait less, until blocks share a
+        // unit and the operands' repeated loads cost more (tiles of 32 x 32, 64 x 32,
+        // 64 x 64: 8 x 8^2, 256 -> 256 channels 12.7, 17.3, 24.2 us; 32 x 8^2, 512 and
+        // 256 blocks of the first two, 20.8, 17.8, 24.4; 8 x 40^2, 384 -> 128, 1600 and
+        // 800, 91, 79, 58).
+        const int co32 = (a.cout + 31) / 32, px32 = (npix + 31) / 32;
+        constexpr size_t R11 = 16 * 64 * sizeof(float);
+        if ((long)px32 * co32 <= 256) {
+            hipLaunchKernelGGL((conv3x3_kernel<1, 1, 4>), dim3(px32, co32), dim3(256), 3 * R11, s, a);
+        } else if ((long)tiles_px * co32 <= 256) {
+            hipLaunchKernelGGL((conv3x3_kernel<WM, 1, 4>), dim3(tiles_px, co32), dim3(256),
+                               3 * WM * R11, s, a);
+        } else {
+            const dim3 grid(tiles_px, tiles_co);
+            hipLaunchKernelGGL((conv3x3_kernel<WM, WN, 4>), grid, dim3(256), 3 * R, s, a);
+        }
     }
     return hipGetLastError();
 }

@@ -33,6 +33,15 @@ def test_conv_shared_tiles(n, h, w, cin, cout):
     check(n, h, w, cin, cout)
 
 
+# the direct kernel's tiles by the number of blocks: one pixel, parts of tiles, 250 blocks of
+# 32 x 32, 188 and 256 of 64 x 32, 258 (which take 64 x 64)
+@pytest.mark.parametrize("n,h,w,cin,cout", [
+    (1, 1, 1, 32, 1), (2, 5, 7, 48, 33), (3, 8, 8, 256, 256), (2, 50, 40, 32, 33),
+    (3, 50, 40, 32, 64), (4, 51, 40, 32, 40), (5, 41, 40, 32, 64)])
+def test_conv_direct_tiles(n, h, w, cin, cout):
+    check(n, h, w, cin, cout)
+
+
 def check(n, h, w, cin, cout):
     import torch
     print("conv tiles", n, h, w, cin, cout, flush=True)
