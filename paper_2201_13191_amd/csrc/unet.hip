@@ -825,12 +825,21 @@ __device__ __forceinline__ bf16x8 read_pixels(const uint16_t *row0, int lane) {
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-#ifndef MCX_WG_DEPTH
-#define MCX_WG_DEPTH 3
-#endif
-constexpr int kWgDepth = MCX_WG_DEPTH;   // staged rows in flight
-
+constexpr int kWgDepth = 3;       // staged rows in flight
 constexpr int kWgWaves = 8;       // of a block
+
+// values added in pairs, whose rounding errors do not pile up as in a row
+template <int N>
+__device__ __forceinline__ float sum_pairs(const float (&v)[N]) {
+    if constexpr (N == 1) {
+        return v[0];
+    } else {
+        float h[N / 2];
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i) h[i] = v[2 * i] + v[2 * i + 1];
+        return sum_pairs(h);
+    }
+}
 
 __global__ void __launch_bounds__(64 * kWgWaves, 2) wgrad9_kernel(const WgradArgs a, int splits) {
     // per wave: an input row slice of 18 pixels and an output-gradient slice of
@@ -944,35 +953,41 @@ __global__ void __launch_bounds__(64 * kWgWaves, 2) wgrad9_kernel(const WgradArg
 #pragma unroll
             for (int h = 0; h < 8; ++h) {
                 const int r = 8 * (wave & 1) + h;
-                float v = lds.sum[q][0][r][lane];
+                float v[kWgWaves];
 #pragma unroll
-                for (int w = 1; w < kWgWaves; ++w) v += lds.sum[q][w][r][lane];
+                for (int w = 0; w < kWgWaves; ++w) v[w] = lds.sum[q][w][r][lane];
                 const int co = co0 + 8 * (r >> 2) + 4 * kh + (r & 3);
-                if (co < a.cout) a.partial[(((size_t)split * 9 + t) * a.cout + co) * a.cin + ci] = v;
+                if (co < a.cout)
+                    a.partial[(((size_t)split * 9 + t) * a.cout + co) * a.cin + ci] =
+                        sum_pairs(v);
             }
         }
     }
 }
 
-// dw[co][tap][ci] from the splits' partial tiles [split][tap][co][ci], summed in
-// order
+// dw[co][tap][ci] from the splits' partial tiles [split][tap][co][ci]: 16
+// running sums, each of every 16th split, and those in pairs
+constexpr int kWgSums = 16;
+
 __global__ void __launch_bounds__(256) wgrad_sum_kernel(const float *partial, int splits, int cout,
                                                         int cin, float *dw) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int n = 9 * cout * cin;
     if (i >= n) return;
     const int ci = i % cin, co = (i / cin) % cout, tap = i / (cin * cout);
-    float s = 0.0f;
+    float s[kWgSums] = {};
     int k = 0;
-    for (; k + 8 <= splits; k += 8) {
-        float v[8];
+    for (; k + kWgSums <= splits; k += kWgSums) {
+        float v[kWgSums];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = partial[(size_t)(k + q) * n + i];
+        for (int q = 0; q < kWgSums; ++q) v[q] = partial[(size_t)(k + q) * n + i];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) s += v[q];
+        for (int q = 0; q < kWgSums; ++q) s[q] += v[q];
     }
-    for (; k < splits; ++k) s += partial[(size_t)k * n + i];
-    dw[((size_t)co * 9 + tap) * cin + ci] = s;
+#pragma unroll
+    for (int q = 0; q < kWgSums; ++q)
+        if (k + q < splits) s[q] += partial[(size_t)(k + q) * n + i];
+    dw[((size_t)co * 9 + tap) * cin + ci] = sum_pairs(s);
 }
 
 // Sum of the splits' partial tiles in a fixed order, in two levels: groups of
@@ -1321,22 +1336,42 @@ hipError_t nn_conv3x3(const ConvArgs &a, hipStream_t s) {
     return conv_launch<2, 2>(a, (a.cout + 63) / 64, s);
 }
 
-#ifndef MCX_WG_BLOCKS
-#define MCX_WG_BLOCKS 256
-#endif
-constexpr int kWgBlocks = MCX_WG_BLOCKS;
+constexpr int kWgBlocks = 256;
+
+// Splits of wgrad9_kernel for `tiles` blocks each, never more than the caller's
+// workspace holds: one block a compute unit (a few more would run after the others:
+// 252 blocks 18.5 us, 264 30.6, 516 of half as many waves 34) with at least 4 slices a
+// wave, or as many rounds of that as keep the rounding error to what the caller's splits
+// give in the other kernel's order (4 waves, then 32 splits, then the groups, each in a
+// row).  The error's variance goes with the terms that are added in a row, and with twice
+// the levels of a sum in pairs; a slice's products go to the accumulator in two halves,
+// each rounded (fp32 sums made in that order on the host have the kernel's very error).
+// 4 x 128^2, 512 -> 64 channels, 32 splits for the caller: one round (8 splits) has 1.18
+// times the rms error of that order, two have 0.91 of it.
+static int wgrad9_splits(int64_t slices, int64_t tiles, int caller) {
+    auto up = [](int64_t x, int64_t y) { return (x + y - 1) / y; };
+    auto row = [](int64_t m) { return m > 1 ? m : 0; };
+    const int64_t most = 2 * up(slices, 4LL * caller) + 4 + row(std::min(caller, kWgGroup)) +
+                         row(up(caller, kWgGroup));
+    auto ours = [&](int64_t k) {
+        const int64_t pairs = k > 8 ? 8 : k > 4 ? 6 : k > 2 ? 4 : k > 1 ? 2 : 0;
+        return 2 * up(slices, kWgWaves * k) + 6 + row(up(k, kWgSums)) + pairs;
+    };
+    int64_t s = std::min<int64_t>(std::max<int64_t>(1, kWgBlocks / tiles), slices / (4 * kWgWaves));
+    s = std::max<int64_t>(1, std::min<int64_t>(s, caller));
+    int64_t best = s;
+    for (int64_t rounds = 2; s < caller && ours(best) > most && s / kWgSums < most; ++rounds) {
+        s = std::min<int64_t>(caller, std::max<int64_t>(s + 1, rounds * kWgBlocks / tiles));
+        if (ours(s) < ours(best)) best = s;
+    }
+    return (int)best;
+}
 
 hipError_t nn_wgrad(const WgradArgs &a, float *tmp, float *dw, hipStream_t s) {
     if (a.w_ % 16 == 0 && (a.ldy | a.yoff) % 8 == 0 && ((uintptr_t)a.dy & 15) == 0) {
-        // one block a compute unit (a few more would run after the others: 252 blocks
-        // 18.5 us, 264 30.6, 516 of half as many waves 34), at least 4 slices a wave, and
-        // never more splits than the caller's workspace holds
-        const int tiles_co = (a.cout + 31) / 32, tiles_ci = (a.cin + 31) / 32;
-        const int64_t slices = (int64_t)a.n * a.h * (a.w_ / 16);
-    const int64_t want = std::max<int64_t>(1, kWgBlocks / (tiles_co * tiles_ci));
-        const int splits = (int)std::max<int64_t>(
-            1, std::min<int64_t>(a.splits, std::min<int64_t>(want, slices / (4 * kWgWaves))));
-        hipLaunchKernelGGL(wgrad9_kernel, dim3(tiles_co * tiles_ci * splits), dim3(64 * kWgWaves), 0, s, a,
+        const int tiles = ((a.cout + 31) / 32) * ((a.cin + 31) / 32);
+        const int splits = wgrad9_splits((int64_t)a.n * a.h * (a.w_ / 16), tiles, a.splits);
+        hipLaunchKernelGGL(wgrad9_kernel, dim3(tiles * splits), dim3(64 * kWgWaves), 0, s, a,
                            splits);
         hipLaunchKernelGGL(wgrad_sum_kernel, dim3(blocks_for((int64_t)9 * a.cout * a.cin)),
                            dim3(256), 0, s, (const float *)a.partial, splits, a.cout, a.cin, dw);
