@@ -802,7 +802,9 @@ __global__ void __launch_bounds__(256) wgrad_kernel(const WgradArgs a) {
 // (one k-step of the matrix product); a wave walks down a 16-pixel column of
 // slices, so that every input row is staged once and meets the three
 // output-gradient rows whose fragments it keeps in registers: 9 products per
-// staged row, from three shifted reads.  Both operands need eight pixels of one
+// staged row, from three shifted reads (fewer at the strip's ends: a product with
+// a row of zeros in place of one that is not the strip's would make NaN of an
+// infinite input).  Both operands need eight pixels of one
 // channel per lane while memory holds channels together: the rows go to LDS as
 // they are and are read transposed (ds_read_b64_tr_b16: lane t of 16 gives the
 // address of row t / 4, columns 4 (t % 4) .. +4, and receives column t of the
@@ -914,7 +916,6 @@ __global__ void __launch_bounds__(64 * kWgWaves, 2) wgrad9_kernel(const WgradArg
         for (int j0 = y0 - 1; j0 <= y1; j0 += kWgDepth) {
 #pragma unroll
             for (int q = 0; q < kWgDepth; ++q) {
-                // (rows past the strip's end are zeros, and change nothing)
                 *(uint4 *)(s_x + lane * 8) = ring[q].x0;
                 if (lane < 8) *(uint4 *)(s_x + (64 + lane) * 8) = ring[q].x1;
                 *(uint4 *)(s_dy + lane * 8) = ring[q].y;
@@ -927,12 +928,18 @@ __global__ void __launch_bounds__(64 * kWgWaves, 2) wgrad9_kernel(const WgradArg
 #pragma unroll
                 for (int k = 0; k < 3; ++k) b[k] = read_pixels(s_x + k * 32, lane);
                 wave_sync();      // the next row overwrites the staging
+                const int j = j0 + q;
+                // (a copy of these without the conditions for the strip's inner rows
+                // puts the accumulators in scratch memory)
+                auto products = [&](int row, bf16x8 av, f32x16 *t) __attribute__((always_inline)) {
+                    if (row < y0 || row >= y1) return;
 #pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    acc[6 + k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b[k], acc[6 + k], 0, 0, 0);
-                    acc[3 + k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b[k], acc[3 + k], 0, 0, 0);
-                    acc[k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, b[k], acc[k], 0, 0, 0);
-                }
+                    for (int k = 0; k < 3; ++k)
+                        t[k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, b[k], t[k], 0, 0, 0);
+                };
+                products(j - 1, a0, acc + 6);
+                products(j, a1, acc + 3);
+                products(j + 1, a2, acc);
             }
         }
     }
