@@ -324,7 +324,9 @@ __global__ void __launch_bounds__(256) conv3x3_kernel(const ConvArgs a) {
 // value is loaded once per chunk instead of once per tap, and 1.5 times in all
 // (with a window of its own per wave every row was staged three times).  The
 // next chunk's loads are in flight in registers while the products of the
-// current one are issued.
+// current one are issued.  OWN: the waves' windows are their own, for heights whose
+// last four rows are mostly past the image (the host's rule says which): four tiles of
+// 64 pixels in a row, across rows and images.
 constexpr int kLdsInPx = 66;                          // staged pixels per row
 constexpr int kLdsInElems = 3 * kLdsInPx * 16;        // one wave's rows, one chunk (bf16)
 
@@ -333,9 +335,10 @@ constexpr int lds_w_elems() { return 9 * 32 * WN * 16; }   // the block's weight
 
 constexpr int kLdsRows = 4;                                // output rows of a block, one a wave
 constexpr int kLdsBlockElems = (kLdsRows + 2) * kLdsInPx * 16;   // staged input, one chunk
-template <int WN>
+template <int WN, bool OWN>
 constexpr size_t conv_lds_bytes() {
-    constexpr size_t chunk = (kLdsBlockElems + lds_w_elems<WN>()) * 2;
+    constexpr size_t chunk =
+        ((OWN ? kLdsRows * kLdsInElems : kLdsBlockElems) + lds_w_elems<WN>()) * 2;
     constexpr size_t epilogue = kLdsRows * 32 * kEpStride * sizeof(float);
     return chunk > epilogue ? chunk : epilogue;
 }
@@ -349,37 +352,43 @@ constexpr bool conv_lds_enabled = MCX_CONV_LDS != 0;
 #endif
 constexpr bool conv_half_tiles = MCX_CONV_HALF_TILES != 0;
 
-template <int WN>
+template <int WN, bool OWN>
 __global__ void __launch_bounds__(256) conv3x3_lds_kernel(const ConvArgs a) {
     constexpr int WM = 2;
-    constexpr int kInItems = (kLdsRows + 2) * kLdsInPx * 2;     // 16-byte items of the window
-    constexpr int kInPer = (kInItems + 255) / 256;
+    // 16-byte items of the window, staged by the wave or by the block
+    constexpr int kInItems = (OWN ? 3 : kLdsRows + 2) * kLdsInPx * 2;
+    constexpr int kInThreads = OWN ? 64 : 256;
+    constexpr int kInPer = (kInItems + kInThreads - 1) / kInThreads;
     constexpr int kWItems = 9 * 32 * WN * 2;                    // and of the weights
     constexpr int kWPer = (kWItems + 255) / 256;
     extern __shared__ __align__(16) float s_dyn[];
-    uint16_t *in = (uint16_t *)s_dyn, *wl = in + kLdsBlockElems;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint16_t *in = (uint16_t *)s_dyn + (OWN ? wave * kLdsInElems : 0);
+    uint16_t *wl = (uint16_t *)s_dyn + (OWN ? kLdsRows * kLdsInElems : kLdsBlockElems);
+    const int in_id = OWN ? lane : (int)threadIdx.x;
     const int kh = lane >> 5, lr = lane & 31;
-    // block: (image, group of 4 rows, 64-pixel segment), segments fastest
-    const int segs = a.w_ >> 6, groups = (a.h + kLdsRows - 1) / kLdsRows;
-    const int rank = (int)xcd_rank(blockIdx.x, gridDim.x);
-    const int x0 = (rank % segs) * 64, y0 = (rank / segs) % groups * kLdsRows;
+    // block: (image, group of 4 rows, 64-pixel segment), segments fastest; or four of
+    // the tiles (image, row, segment)
+    const int segs = a.w_ >> 6, groups = OWN ? a.h : (a.h + kLdsRows - 1) / kLdsRows;
+    const int rank = (int)xcd_rank(blockIdx.x, gridDim.x) * (OWN ? 4 : 1) + (OWN ? wave : 0);
+    const int x0 = (rank % segs) * 64, y0 = (rank / segs) % groups * (OWN ? 1 : kLdsRows);
     const int img = rank / (segs * groups);
     const int co0 = blockIdx.y * (32 * WN);
     const int npix = a.n * a.h * a.w_;
-    const int px0 = (img * a.h + y0 + wave) * a.w_ + x0;
-    const bool live = y0 + wave < a.h;      // no early return: the block meets at barriers
+    const int px0 = (img * a.h + y0 + (OWN ? 0 : wave)) * a.w_ + x0;
+    // no early return: the block meets at barriers
+    const bool live = OWN ? img < a.n : y0 + wave < a.h;
     const int kc = a.cin >> 4;
     const size_t wk = (size_t)9 * a.cin;
     uint4 rin[kInPer], rw[kWPer];
     auto load_chunk = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
         for (int m = 0; m < kInPer; ++m) {
-            const int t = threadIdx.x + 256 * m;
+            const int t = in_id + kInThreads * m;
             const int q = t >> 1, r = q / kLdsInPx, px = q - r * kLdsInPx;
             const int y2 = y0 + r - 1, x2 = x0 + px - 1;
             rin[m] = make_uint4(0u, 0u, 0u, 0u);
-            if (t < kInItems && y2 >= 0 && y2 < a.h && x2 >= 0 && x2 < a.w_)
+            if ((!OWN || live) && t < kInItems && y2 >= 0 && y2 < a.h && x2 >= 0 && x2 < a.w_)
                 rin[m] = *(const uint4 *)(a.x + ((size_t)(img * a.h + y2) * a.w_ + x2) * a.ldx +
                                           a.xoff + c * 16 + (t & 1) * 8);
         }
@@ -396,7 +405,7 @@ __global__ void __launch_bounds__(256) conv3x3_lds_kernel(const ConvArgs a) {
     auto store_chunk = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int m = 0; m < kInPer; ++m) {
-            const int t = threadIdx.x + 256 * m;
+            const int t = in_id + kInThreads * m;
             if (t < kInItems) *(uint4 *)(in + t * 8) = rin[m];
         }
 #pragma unroll
@@ -415,7 +424,7 @@ __global__ void __launch_bounds__(256) conv3x3_lds_kernel(const ConvArgs a) {
     load_chunk(0);
     store_chunk();
     __syncthreads();
-    const uint16_t *mine = in + wave * kLdsInPx * 16;     // this wave's three rows
+    const uint16_t *mine = in + (OWN ? 0 : wave * kLdsInPx * 16);     // this wave's three rows
     for (int c = 0; c < kc; ++c) {
         if (c + 1 < kc) load_chunk(c + 1);
 #pragma unroll
@@ -1262,8 +1271,19 @@ static hipError_t conv_launch(const ConvArgs &a, int tiles_co, hipStream_t s) {
     const int K = 9 * (a.cin / 16);
     constexpr size_t R = WM * WN * 16 * 64 * sizeof(float);   // one partial tile
     if (WM == 2 && tiles >= 2048 && a.w_ % 64 == 0 && conv_lds_enabled) {
-        const dim3 grid(a.n * ((a.h + kLdsRows - 1) / kLdsRows) * (a.w_ / 64), tiles_co);
-        hipLaunchKernelGGL((conv3x3_lds_kernel<WN>), grid, dim3(256), conv_lds_bytes<WN>(), s, a);
+        // Rows staged for the block, unless its groups of four rows have more than half
+        // as many rows again as the image: heights 1, 2 and 5 (1024 x 1 x 128, 32 -> 64
+        // channels 27.1 us, 15.3 with windows of the waves' own; 512 x 2 x 128 19.5 and
+        // 15.3; 205 x 5 x 128 23.3 and 22.7; 342 x 3 x 128 16.2 and 22.7).
+        const int groups = (a.h + kLdsRows - 1) / kLdsRows;
+        if (2L * kLdsRows * groups > 3L * a.h) {
+            hipLaunchKernelGGL((conv3x3_lds_kernel<WN, true>), dim3((tiles_px + 3) / 4, tiles_co),
+                               dim3(256), (conv_lds_bytes<WN, true>()), s, a);
+        } else {
+            hipLaunchKernelGGL((conv3x3_lds_kernel<WN, false>),
+                               dim3(a.n * groups * (a.w_ / 64), tiles_co), dim3(256),
+                               (conv_lds_bytes<WN, false>()), s, a);
+        }
     } else if (tiles >= 2048 || K < 8) {
         const dim3 grid((tiles_px + 3) / 4, tiles_co);
         hipLaunchKernelGGL((conv3x3_kernel<WM, WN, 1>), grid, dim3(256),
