@@ -461,17 +461,18 @@ __global__ void __launch_bounds__(256) conv3x3_lds_kernel(const ConvArgs a) {
 // waves of a block (16-channel chunks c = ks, ks + KS, ...; partial tiles added
 // in LDS in a fixed order).  Each wave stages its chunk's input window in its
 // own LDS rows; the chunk's weights (nine taps) are loaded into registers
-// through L1/L2 at once, for 32 channels: weights for 64 held 232 registers, two
-// waves a SIMD, and gave half as many blocks (in a forward pass on 8 maps, back to
-// back: the whole 291 -> 270 us, the first split layer 13.9 -> 9.5).  The window is
+// through L1/L2 at once, for 32 * WN channels: weights for 64 leave two waves a
+// SIMD and give half as many blocks (in a forward pass on 8 maps, back to
+// back, with 64 and 32: the whole 291 and 270 us, the first split layer 13.9 and 9.5),
+// which only long reductions in well-filled rounds make up for.  The window is
 // the tile's image rows and one more on each side: for widths that are multiples of 64 one row of 66 pixels, for
 // widths of 16 or 32 (a 64-pixel tile is 4 or 2 whole rows) the rows at their
 // full width plus the zero columns at both ends.
-template <int WM, int KS>
+template <int WM, int WN, int KS>
 __global__ void __launch_bounds__(256) conv3x3_lds_split_kernel(const ConvArgs a) {
     constexpr int TPB = 4 / KS;
     constexpr int TPX = 32 * WM;                      // pixels per tile
-    constexpr int R = WM * 16;                        // floats per lane of a partial tile
+    constexpr int R = WM * WN * 16;                        // floats per lane of a partial tile
     constexpr int kInPer = (3 * (TPX + 2) * 2 + 63) / 64;
     static_assert(3 * (TPX + 2) <= 3 * kLdsInPx, "a window fits a wave's rows");
     static_assert(32 * kEpStride <= (KS - 1) * R * 64, "epilogue staging fits a tile's partials");
@@ -482,7 +483,7 @@ __global__ void __launch_bounds__(256) conv3x3_lds_split_kernel(const ConvArgs a
     uint16_t *in = (uint16_t *)s_dyn + wave * kLdsInElems;
     const int npix = a.n * a.h * a.w_;
     const int px0 = ((int)xcd_rank(blockIdx.x, gridDim.x) * TPB + tile) * (32 * WM);
-    const int co0 = blockIdx.y * 32;
+    const int co0 = blockIdx.y * (32 * WN);
     const bool live = px0 < npix;       // no early return: the block meets at barriers
     const bool wide = a.w_ >= TPX;
     const int nr = wide ? 1 : TPX / a.w_;             // image rows of the tile
@@ -501,11 +502,13 @@ __global__ void __launch_bounds__(256) conv3x3_lds_split_kernel(const ConvArgs a
     }
     const int kc = a.cin >> 4;
     const size_t wk = (size_t)9 * a.cin;
-    f32x16 acc[WM][1];
+    f32x16 acc[WM][WN];
 #pragma unroll
     for (int i = 0; i < WM; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][0][r] = 0.0f;
+        for (int j = 0; j < WN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
     uint4 rin[kInPer];
     auto load_chunk = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
@@ -524,11 +527,13 @@ __global__ void __launch_bounds__(256) conv3x3_lds_split_kernel(const ConvArgs a
         for (int c = ks; c < kc; c += KS) {
             // the chunk's nine taps of weights, all in flight at once (one wait
             // per chunk rather than one per tap)
-            bf16x8 bw[9];
+            bf16x8 bw[9][WN];
 #pragma unroll
             for (int tap = 0; tap < 9; ++tap)
-                bw[tap] = *(const bf16x8 *)(a.w + (size_t)(co0 + lr) * wk +
-                                            (size_t)tap * a.cin + c * 16 + kh * 8);
+#pragma unroll
+                for (int j = 0; j < WN; ++j)
+                    bw[tap][j] = *(const bf16x8 *)(a.w + (size_t)(co0 + j * 32 + lr) * wk +
+                                                   (size_t)tap * a.cin + c * 16 + kh * 8);
 #pragma unroll
             for (int m = 0; m < kInPer; ++m) {
                 const int t = lane + 64 * m;
@@ -546,8 +551,10 @@ __global__ void __launch_bounds__(256) conv3x3_lds_split_kernel(const ConvArgs a
                         av[i] = *(const bf16x8 *)(in + (aoff[i] + r * wn + k) * 16 + kh * 8);
 #pragma unroll
                     for (int i = 0; i < WM; ++i)
-                        acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                            av[i], bw[3 * r + k], acc[i][0], 0, 0, 0);
+#pragma unroll
+                        for (int j = 0; j < WN; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                                av[i], bw[3 * r + k][j], acc[i][j], 0, 0, 0);
                 }
             wave_sync();      // the next chunk overwrites the rows
         }
@@ -560,7 +567,9 @@ __global__ void __launch_bounds__(256) conv3x3_lds_split_kernel(const ConvArgs a
 #pragma unroll
         for (int i = 0; i < WM; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) mine[(i * 16 + r) * 64 + lane] = acc[i][0][r];
+            for (int j = 0; j < WN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) mine[((i * WN + j) * 16 + r) * 64 + lane] = acc[i][j][r];
     }
     __syncthreads();
     if (ks > 0) return;
@@ -570,17 +579,19 @@ __global__ void __launch_bounds__(256) conv3x3_lds_split_kernel(const ConvArgs a
 #pragma unroll
         for (int i = 0; i < WM; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                acc[i][0][r] += base[((size_t)q * R + i * 16 + r) * 64 + lane];
+            for (int j = 0; j < WN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    acc[i][j][r] += base[((size_t)q * R + (i * WN + j) * 16 + r) * 64 + lane];
     }
     if (!live) return;
-    conv_epilogue<WM, 1>(a, acc, px0, co0, npix, (float *)base, lane);
+    conv_epilogue<WM, WN>(a, acc, px0, co0, npix, (float *)base, lane);
 }
 
-template <int WM, int KS>
+template <int WM, int WN, int KS>
 constexpr size_t conv_lds_split_bytes() {
     constexpr size_t rows = 4 * kLdsInElems * 2;
-    constexpr size_t parts = (size_t)(4 / KS) * (KS - 1) * WM * 16 * 64 * sizeof(float);
+    constexpr size_t parts = (size_t)(4 / KS) * (KS - 1) * WM * WN * 16 * 64 * sizeof(float);
     return rows > parts ? rows : parts;
 }
 
@@ -1306,9 +1317,25 @@ static hipError_t conv_launch(const ConvArgs &a, int tiles_co, hipStream_t s) {
             return a.cin % 64 == 0 && blocks >= 256 && (blocks <= 512 || a.cin >= long_cin);
         };
         if (tiles >= 1024 || a.cin < 64) {
+            if constexpr (WN == 2) {
+                // Tiles of 64 channels read the input half as often, which long reductions
+                // feel (64 and 32 channels a tile, 4 x 64^2, 128 -> 256: 29.2 / 29.8 us, 192
+                // 39.6 / 42.0, 384 71.5 / 80.7), where no part of a tile is empty and their
+                // blocks leave the compute units little idle at the end (384 -> 64 channels:
+                // 544 blocks 105 / 98, 640 107 / 104, 704 109 / 118, 768 114 / 123, 832 141 /
+                // 138, 896 142 / 143, 960 142 / 157; 768 -> 64: 896 blocks 260 / 282)
+                const long blocks = (long)((tiles_px + 1) / 2) * tiles_co;
+                const double fill = (double)blocks / ((blocks + 255) / 256 * 256);
+                if (a.cin > 128 && co32 % 2 == 0 && fill >= (a.cin < 512 ? 0.9 : 0.875)) {
+                    hipLaunchKernelGGL((conv3x3_lds_split_kernel<2, 2, 2>),
+                                       dim3((tiles_px + 1) / 2, tiles_co), dim3(256),
+                                       (conv_lds_split_bytes<2, 2, 2>()), s, a);
+                    return hipGetLastError();
+                }
+            }
             const dim3 grid((tiles_px + 1) / 2, co32);
-            hipLaunchKernelGGL((conv3x3_lds_split_kernel<2, 2>), grid, dim3(256),
-                               (conv_lds_split_bytes<2, 2>()), s, a);
+            hipLaunchKernelGGL((conv3x3_lds_split_kernel<2, 1, 2>), grid, dim3(256),
+                               (conv_lds_split_bytes<2, 1, 2>()), s, a);
         } else {
             if constexpr (WN == 2) {
                 if (conv_half_tiles && tiles < 512 && a.cin <= 256) {
@@ -1320,8 +1347,8 @@ static hipError_t conv_launch(const ConvArgs &a, int tiles_co, hipStream_t s) {
                         hipLaunchKernelGGL((conv3x3_lds_shared_kernel<1>), grid, dim3(256),
                                            conv_lds_shared_bytes<1>(), s, a);
                     else
-                        hipLaunchKernelGGL((conv3x3_lds_split_kernel<1, 4>), grid, dim3(256),
-                                           (conv_lds_split_bytes<1, 4>()), s, a);
+                        hipLaunchKernelGGL((conv3x3_lds_split_kernel<1, 1, 4>), grid, dim3(256),
+                                           (conv_lds_split_bytes<1, 1, 4>()), s, a);
                     return hipGetLastError();
                 }
             }
@@ -1330,8 +1357,8 @@ static hipError_t conv_launch(const ConvArgs &a, int tiles_co, hipStream_t s) {
                 hipLaunchKernelGGL((conv3x3_lds_shared_kernel<2>), grid, dim3(256),
                                    conv_lds_shared_bytes<2>(), s, a);
             else
-                hipLaunchKernelGGL((conv3x3_lds_split_kernel<2, 4>), grid, dim3(256),
-                                   (conv_lds_split_bytes<2, 4>()), s, a);
+                hipLaunchKernelGGL((conv3x3_lds_split_kernel<2, 1, 4>), grid, dim3(256),
+                                   (conv_lds_split_bytes<2, 1, 4>()), s, a);
         }
     } else if (tiles >= 1024 || K < 16) {
         const dim3 grid((tiles_px + 1) / 2, tiles_co);
