@@ -30,6 +30,8 @@
 // wave or round runs it, and images do not depend on the launch shape.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "fp64_math.hpp"
 #include "kernel_params.hpp"
 
@@ -1818,7 +1820,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) p
     const VoxelGrid &gr = p.G;
     const int rays = sub * sub, per_block = primary_pixels(sub);
     const double da = (double)p.pu * (double)p.pv / ((double)sub * sub);
-    const int pix0 = blockIdx.x * per_block;
+    const int pix0 = (int)(blockIdx.y * gridDim.x + blockIdx.x) * per_block;
+    if (pix0 >= p.nu * p.nv) return;
     const int n_pix = min(per_block, p.nu * p.nv - pix0);
     double acc = 0.0;       // of pixel pix0 + lane, on the first wave
     for (int r0 = 0; r0 < rays; r0 += kPrimRays) {
@@ -1934,11 +1937,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) p
 hipError_t launch_primary(const KParams &p, int sub, const double *bin_w, const float *bin_mu,
                           int n_bins, float *out, hipStream_t stream) {
     const int per_block = primary_pixels(sub);
-    const int grid = (p.nu * p.nv + per_block - 1) / per_block;
+    // a launch has fewer than 2^32 threads along x: the blocks of a large panel go on along y
+    const int blocks = (p.nu * p.nv + per_block - 1) / per_block;
+    const int bx = std::min(1 << 20, blocks);
+    const dim3 grid(bx, (blocks + bx - 1) / bx);
     const size_t lds = (160 + (size_t)kPrimParts * kPrimRays * (1 + p.n_mat)) * sizeof(double);
     auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), lds, stream, p, sub, bin_w, bin_mu,
-                           n_bins, out);
+        hipLaunchKernelGGL(kernel, grid, dim3(256), lds, stream, p, sub, bin_w, bin_mu, n_bins,
+                           out);
         return hipGetLastError();
     };
     // the default set has 5 materials; each of the 16 possible ones would hold
