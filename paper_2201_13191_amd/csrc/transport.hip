@@ -31,6 +31,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "fp64_math.hpp"
 #include "kernel_params.hpp"
@@ -1784,33 +1785,32 @@ hipError_t launch_march_probe(const KParams &p, int layout, int grid, int block,
 // Latency bounds it at the usual panel sizes (128^2 pixels x 4 rays are 1024
 // waves).  A thread per pixel left three quarters of the chip idle and waited
 // for every step's gather and sum in turn (233 us for that panel through 64^3,
-// 119 bins).  A block takes 64 rays: its four waves each march a quarter of
+// 119 bins).  A block takes 64 rays at a time: its four waves each march a quarter of
 // the rays' steps in groups of 8 gathers, adding to their own columns with LDS
 // atomics that return nothing, and each evaluate a quarter of the bins; the
 // parts are added in a fixed order, and a pixel's rays in row order: 25 us,
 // with the registers held to four waves a SIMD, which the 1024 blocks then fill
-// at once (three: 31 us; eight parts: 40 us).
+// at once (three: 31 us; eight parts: 40 us).  Large panels fill the chip without that,
+// and every wave of a block sets up its rays and gathers their paths: there a
+// block is one wave, and takes enough pixels that their rays fill its rounds of 64
+// (1024^2 pixels of 36 rays, one bin: a thread per pixel 2.12 ms, four waves and a pixel
+// a block 6.49, now 1.38).
 constexpr int kPrimRays = 64;     // rays of a block at a time, one per lane
 constexpr int kPrimParts = 4;     // waves: shares of the steps and of the bins
 
-// pixels of a block: whole pixels' rays in 64 lanes, or one pixel in rounds
-__host__ __device__ inline int primary_pixels(int sub) {
-    return sub * sub < kPrimRays ? kPrimRays / (sub * sub) : 1;
-}
-
-template <int MODE, int MAXM>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) primary_kernel(const KParams p, int sub,
-                                                      const double *bin_w, const float *bin_mu,
-                                                      int n_bins, float *out) {
+template <int MODE, int MAXM, int PARTS>
+__global__ void __launch_bounds__(64 * PARTS) __attribute__((amdgpu_waves_per_eu(4)))
+primary_kernel(const KParams p, int sub, int per_block, const double *bin_w, const float *bin_mu,
+               int n_bins, float *out) {
     extern __shared__ double plds[];
     float *s_pal_rho = (float *)plds;                     // [256]
     uint8_t *s_pal_id = (uint8_t *)(s_pal_rho + 256);     // [256]
-    double *s_val = plds + 160;                           // [kPrimParts][kPrimRays]
-    double *s_lam = s_val + kPrimParts * kPrimRays;       // [kPrimParts][n_mat][kPrimRays]
+    double *s_val = plds + 160;                           // [PARTS][kPrimRays]
+    double *s_lam = s_val + PARTS * kPrimRays;            // [PARTS][n_mat][kPrimRays]
     const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
     double *lam = s_lam + (size_t)part * p.n_mat * kPrimRays + lane;
     if (MODE != kGeneric) {
-        for (int i = threadIdx.x; i < p.G.n_pal; i += 256) {
+        for (int i = threadIdx.x; i < p.G.n_pal; i += 64 * PARTS) {
             s_pal_rho[i] = p.G.pal_rho[i];
             s_pal_id[i] = p.G.pal_id[i];
         }
@@ -1818,16 +1818,21 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) p
     __syncthreads();
     const ProjFrame &F = p.F;
     const VoxelGrid &gr = p.G;
-    const int rays = sub * sub, per_block = primary_pixels(sub);
+    const int rays = sub * sub;
     const double da = (double)p.pu * (double)p.pv / ((double)sub * sub);
     const int pix0 = (int)(blockIdx.y * gridDim.x + blockIdx.x) * per_block;
     if (pix0 >= p.nu * p.nv) return;
     const int n_pix = min(per_block, p.nu * p.nv - pix0);
     double acc = 0.0;       // of pixel pix0 + lane, on the first wave
-    for (int r0 = 0; r0 < rays; r0 += kPrimRays) {
+    // rounds of 64 rays: of whole pixels or of a part of one, or (one wave a block) of the
+    // pixels' rays one after the other
+    const bool flat = PARTS == 1 && per_block > 1;
+    const int total = flat ? n_pix * rays : rays;
+    for (int r0 = 0; r0 < total; r0 += kPrimRays) {
         // this lane's pixel and ray
-        const int mine = per_block > 1 ? lane / rays : 0;
-        const int ray = per_block > 1 ? lane - mine * rays : r0 + lane;
+        const int at = flat ? r0 + lane : lane;
+        const int mine = per_block > 1 ? at / rays : 0;
+        const int ray = per_block > 1 ? at - mine * rays : r0 + lane;
         const bool live = mine < n_pix && ray < rays;
         const int pix = pix0 + (live ? mine : 0);
         const int iu = pix % p.nu, iv = pix / p.nu;
@@ -1860,7 +1865,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) p
             const float L = tout - tin;
             // a quarter of the steps, from an anchor
             const uint32_t n = step_count(L, p.step);
-            const uint32_t share = ((n + 4 * kPrimParts - 1) / (4 * kPrimParts)) * 4;
+            const uint32_t share = ((n + 4 * PARTS - 1) / (4 * PARTS)) * 4;
             const uint32_t k1 = min(n, (part + 1) * share);
             for (uint32_t k = part * share; k < k1; k += kPrefetch) {
                 uint32_t code[kPrefetch];
@@ -1900,11 +1905,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) p
             path[m] = 0.0;
             if (m < p.n_mat)
 #pragma unroll
-                for (int t = 0; t < kPrimParts; ++t)
+                for (int t = 0; t < PARTS; ++t)
                     path[m] += s_lam[(t * p.n_mat + m) * kPrimRays + lane];
         }
         double e_sum = 0.0;
-        const int bins = (n_bins + kPrimParts - 1) / kPrimParts;
+        const int bins = (n_bins + PARTS - 1) / PARTS;
         const int b1 = min(n_bins, (part + 1) * bins);
 #pragma unroll 4
         for (int k = part * bins; k < b1; ++k) {
@@ -1920,12 +1925,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) p
         s_val[part * kPrimRays + lane] = e_sum * (ax * da / r2);
         __syncthreads();
         if (part == 0 && lane < n_pix) {
-            const int first = per_block > 1 ? lane * rays : 0;
-            const int count = per_block > 1 ? rays : min(kPrimRays, rays - r0);
+            const int first = flat ? max(lane * rays - r0, 0) : per_block > 1 ? lane * rays : 0;
+            const int count = flat ? min((lane + 1) * rays - r0, kPrimRays) - first
+                                   : per_block > 1 ? rays : min(kPrimRays, rays - r0);
             for (int t = 0; t < count; ++t) {
                 double ray_sum = 0.0;
 #pragma unroll
-                for (int q = 0; q < kPrimParts; ++q) ray_sum += s_val[q * kPrimRays + first + t];
+                for (int q = 0; q < PARTS; ++q) ray_sum += s_val[q * kPrimRays + first + t];
                 acc += ray_sum;
             }
         }
@@ -1936,25 +1942,45 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) p
 
 hipError_t launch_primary(const KParams &p, int sub, const double *bin_w, const float *bin_mu,
                           int n_bins, float *out, hipStream_t stream) {
-    const int per_block = primary_pixels(sub);
-    // a launch has fewer than 2^32 threads along x: the blocks of a large panel go on along y
-    const int blocks = (p.nu * p.nv + per_block - 1) / per_block;
-    const int bx = std::min(1 << 20, blocks);
-    const dim3 grid(bx, (blocks + bx - 1) / bx);
-    const size_t lds = (160 + (size_t)kPrimParts * kPrimRays * (1 + p.n_mat)) * sizeof(double);
-    auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, dim3(256), lds, stream, p, sub, bin_w, bin_mu, n_bins,
-                           out);
+    const int rays = sub * sub, pixels = p.nu * p.nv;
+    const bool few = p.n_mat <= 5;
+    auto launch = [&](auto kernel, int parts, int per_block) {
+        // a launch has fewer than 2^32 threads along x: the blocks of a large panel go on
+        // along y
+        const int blocks = (pixels + per_block - 1) / per_block;
+        const int bx = std::min(1 << 20, blocks);
+        const size_t lds = (160 + (size_t)parts * kPrimRays * (1 + p.n_mat)) * sizeof(double);
+        hipLaunchKernelGGL(kernel, dim3(bx, (blocks + bx - 1) / bx), dim3(64 * parts), lds, stream,
+                           p, sub, per_block, bin_w, bin_mu, n_bins, out);
         return hipGetLastError();
     };
     // the default set has 5 materials; each of the 16 possible ones would hold
     // two registers of path
-    const bool few = p.n_mat <= 5;
-    if (p.G.layout == kGeneric)
-        return few ? launch(primary_kernel<kGeneric, 5>)
-                   : launch(primary_kernel<kGeneric, kMaxMaterials>);
-    return few ? launch(primary_kernel<kPaletteLane, 5>)
-               : launch(primary_kernel<kPaletteLane, kMaxMaterials>);
+    auto layout = [&](auto parts, int per_block) {
+        constexpr int P = decltype(parts)::value;
+        if (p.G.layout == kGeneric)
+            return few ? launch(primary_kernel<kGeneric, 5, P>, P, per_block)
+                       : launch(primary_kernel<kGeneric, kMaxMaterials, P>, P, per_block);
+        return few ? launch(primary_kernel<kPaletteLane, 5, P>, P, per_block)
+                   : launch(primary_kernel<kPaletteLane, kMaxMaterials, P>, P, per_block);
+    };
+    // the fewest pixels whose rays fill nine tenths of their rounds of 64
+    const int whole = std::max(1, kPrimRays / rays);
+    int filled = whole;
+    while (10 * filled * rays < 9 * ((filled * rays + kPrimRays - 1) / kPrimRays * kPrimRays))
+        ++filled;
+    // One wave a block once the rays' waves alone fill the SIMDs four deep, later with
+    // many steps to share out and sooner with few and hardly a bin (one and four waves a
+    // block: 64^3 and 119 bins, 2048 waves 51.9 and 40.6 us, 4096 72.4 and 76.4, 9216 140
+    // and 162; 192^3 4096 102 and 96, 8192 161 and 171; 32^3 and one bin, 1024 waves 9.7
+    // and 10.6, 2048 11.6 and 15.2) -- and if there are blocks enough (16^2 pixels of
+    // 4096 rays 2711 and 1093)
+    const int64_t waves = ((int64_t)pixels * rays + kPrimRays - 1) / kPrimRays;
+    const float steps = (float)std::max(p.G.nx, std::max(p.G.ny, p.G.nz)) / (p.G.inv_h * p.step);
+    const int64_t line = steps + (float)n_bins <= 64.0f ? 2048 : steps <= 128.0f ? 4096 : 8192;
+    if (waves < line || (pixels + filled - 1) / filled < 2048)
+        return layout(std::integral_constant<int, kPrimParts>{}, whole);
+    return layout(std::integral_constant<int, 1>{}, filled);
 }
 
 // Angular interpolation (section II-C-3): scatter maps simulated at every
