@@ -56,9 +56,9 @@ __device__ __forceinline__ double row_height2(const FdkGeom &g, double s, int r)
 
 // The discrete Ram-Lak filter of the virtual pitch t: h(0) = 1/(4 t^2),
 // h(odd d) = -1/(d pi t)^2, h(even d) = 0, times t.  One block per panel row,
-// the weighted row in LDS.  Only for rows wider than one block of the matrix
-// form below that are filtered in place (it reads a whole row before it
-// writes any of it).
+// the weighted row in LDS: for rows wider than one block of the matrix form
+// below that are filtered in place (it reads a whole row before it writes any
+// of it), and for few and short rows (launch_fdk).
 __global__ void fdk_filter_row_kernel(const float *proj, FdkGeom g, float *q) {
     extern __shared__ double row[];
     const int r = blockIdx.x % g.nv, i = blockIdx.x / g.nv;
@@ -394,12 +394,32 @@ hipError_t launch_fdk(const float *proj, double R, double D, double pu, double p
                         (unsigned)((pairs + block_pairs - 1) / block_pairs));
         hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, proj, g, rows, q);
     };
+    const bool in_place = (const float *)q == proj;
     // The block's width follows the row's (16-pair tiles past the row are
     // computed for nothing), with as few rows as four waves then need: short
     // panels have few blocks (180 x 128^2: 64-row blocks, 1.4 a compute unit,
     // took 28.8 us, 32-row ones 20 us).  Rows above 512 pixels take several
     // blocks, which read what others would overwrite in place.
-    if (pairs <= 32)
+    //   Few rows leave a block's own length to wait for: then its columns are shared out
+    // over blocks of 32 x 64 while these run two to a compute unit (with the
+    // backprojection of one voxel, 66 rows of 130 pixels 30.0 and 15.4 us, 3840 of 192
+    // 40.8 and 25.2, 7680 of 256 45.1 and 44.0, 16384 of 192 71.5 and 70.3, 16384 of 512 143 and
+    // 163), or, where that cannot be or rows are short, a block takes a row (164 rows of 80
+    // pixels 10.9 and 12.6 us in 32 x 64, 306 of 100 14.2 and 13.4; in place, 924 rows of
+    // 130 20.6 and 33.3 in 64 x 192, 387 of 256 25.2 and 25.5).
+    const bool row_form = pairs > 48 && !in_place ? false
+                          : pairs <= 48           ? rows <= 256
+                          : pairs <= 64           ? false
+                          : pairs <= 96           ? rows <= 1024
+                          : pairs <= 128          ? rows <= 400
+                                                  : pairs > 256;
+    const int64_t narrow = (int64_t)((rows + 31) / 32) * ((pairs + 63) / 64);
+    if (row_form)
+        hipLaunchKernelGGL(fdk_filter_row_kernel, dim3((unsigned)rows), dim3(256),
+                           (size_t)nu * sizeof(double), s, proj, g, q);
+    else if (narrow < 512 && (pairs <= 64 || !in_place))
+        filter(fdk_filter_kernel<1, 4, 1>, 32, 64);
+    else if (pairs <= 32)
         filter(fdk_filter_kernel<2, 2, 1>, 64, 32);
     else if (pairs <= 64)
         filter(fdk_filter_kernel<1, 4, 1>, 32, 64);
@@ -409,11 +429,8 @@ hipError_t launch_fdk(const float *proj, double R, double D, double pu, double p
         filter(fdk_filter_kernel<1, 4, 2>, 32, 128);
     else if (pairs <= 192)
         filter(fdk_filter_kernel<1, 4, 3>, 32, 192);
-    else if (pairs <= 256 || (const float *)q != proj)
-        filter(fdk_filter_kernel<1, 4, 4>, 32, 256);
     else
-        hipLaunchKernelGGL(fdk_filter_row_kernel, dim3((unsigned)rows), dim3(256),
-                           (size_t)nu * sizeof(double), s, proj, g, q);
+        filter(fdk_filter_kernel<1, 4, 4>, 32, 256);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int64_t plane = (int64_t)nx * ny;
