@@ -93,8 +93,10 @@ struct JobDesc {
 };
 
 struct KParams {
-    // voxel object (single projection)
+    // voxel object (single projection), and the share of its cells of 4^3 voxels that
+    // are not uniform
     VoxelGrid G;
+    float mixed;
     // tables on E_j = 1 + j keV: mu/rho [J][n_mat] (photoelectric, Rayleigh, Compton, 0),
     // eta[J]
     const float4 *mu4;

@@ -109,8 +109,9 @@ struct Phantom {
     uint8_t *d_vox = nullptr;
     float *d_vrho = nullptr;
     unsigned char *d_pal = nullptr;     // 256 densities (f32) then 256 ids (u8)
-    uint16_t *d_cells = nullptr;        // uniform-cell map (palette layouts)
+    uint16_t *d_cells = nullptr;        // uniform-cell map
     int ncx = 0, ncy = 0, ncz = 0;
+    float mixed = 0.0f;                 // share of the cells that are not uniform
     bool loaded = false;
 
     void release() {
@@ -479,6 +480,7 @@ mc_status prepare(mc_ctx *c, float beta, uint64_t first, uint64_t n, uint64_t se
     if (rc) return rc;
     common_params(c, p);
     p.G = grid_of(c, ph);
+    p.mixed = ph.mixed;
     p.F = frame_of(c->g, beta);
     p.first = first;
     p.n = n;
@@ -816,6 +818,9 @@ mc_status build_phantom(mc_ctx *c, const uint8_t *ids, const float *rho, int nx,
     HIP_TRY(c, hipMemcpy(out.d_cells, cells.data(), cells.size() * sizeof(uint16_t),
                          hipMemcpyHostToDevice));
     out.ncx = ncx; out.ncy = ncy; out.ncz = ncz;
+    size_t n_mixed = 0;
+    for (const int16_t code : cell_code) n_mixed += code < 0 ? 1u : 0u;
+    out.mixed = (float)n_mixed / (float)cell_code.size();
     out.nx = nx; out.ny = ny; out.nz = nz; out.h = h;
     out.nbx = nbx; out.nby = nby; out.nbz = nbz;
     out.edge_pad = edge_pad;

@@ -1695,18 +1695,24 @@ size_t batch_lds_bytes(const KParams &p, int max_lane_palette, int block) {
            (size_t)max_lane_palette * block * sizeof(double);
 }
 
-// Objects whose voxels fill much more than the L2s take 4 steps at a time: with
-// most steps taken in uniform runs, the tail of a group of 8 fetches lines that
-// a run would have skipped, and those fetches bound them (2e7 photons, groups
+// Objects whose voxels fill much more than the L2s take 4 steps at a time if most
+// steps are taken in uniform runs: the tail of a group of 8 fetches lines that a run
+// would have skipped, and those fetches bound them (2e7 photons, ellipsoids in air, groups
 // of 8 and 4: 512^3 codes 3.71 and 3.57 ms, 448^3 3.50 and 3.46, 384^3 3.31 and
 // 3.33, 256^3 3.00 and 3.06; ids and densities at 5 bytes a voxel, 384^3 7.73
-// and 7.08, 256^3 5.35 and 4.75, 93^3 0.71 and 0.75).  Analog single
-// projections only: the others keep one kernel each.
+// and 7.08, 256^3 5.35 and 4.75, 93^3 0.71 and 0.75).  Where the rays stay in mixed
+// cells, the latency of twice as many groups costs more than that (4e6 photons, a
+// cylinder of noise that fills the share `mixed` of the cells: ids and densities, 448^3
+// 0.13 1.53 and 1.50, 0.28 2.54 and 2.60, 0.5 3.73 and 4.02, 1 5.36 and 5.96; codes, 512^3 0.07 0.73
+// and 0.78, 0.28 1.36 and 1.43; 8e6, cylinder and ellipsoids 0.02 .. 0.054 1.53 / 1.47 ..
+// 1.88 / 1.84, 448^3 0.063 1.72 and 1.75).  Analog single projections only: the
+// others keep one kernel each.
 constexpr int kBigGroup = 4;
 constexpr uint64_t kBigBytes = (uint64_t)64 << 20;
 static bool big_object(const KParams &p, int layout) {
     const uint64_t voxels = (uint64_t)p.G.nx * p.G.ny * p.G.nz;
-    return voxels * (layout == kGeneric ? 5 : 1) > kBigBytes;
+    return layout == kGeneric ? voxels * 5 > kBigBytes && p.mixed <= 0.25f
+                              : voxels > kBigBytes && p.mixed <= 0.06f;
 }
 
 // the kernel with or without the binding-effect samplers, as p.phys asks
