@@ -26,7 +26,7 @@
 namespace mcx {
 hipError_t launch_march_probe(const KParams &p, int layout, int grid, int block,
                               unsigned long long *sum, hipStream_t stream);
-int march_probe_blocks_per_cu(int layout, int block);
+int march_probe_blocks_per_cu(const KParams &p, int layout, int block);
 hipError_t launch_atomic_probe(unsigned long long *img, uint32_t n_pix, unsigned long long n,
                                uint32_t seed, int grid, hipStream_t stream);
 hipError_t launch_transport(const KParams &p, int layout, int grid, int block, bool stats,
@@ -1131,7 +1131,7 @@ mc_status mc_march_probe_async(mc_ctx *c, float beta, uint64_t n_rays, uint64_t 
     // the probe's own occupancy (it uses no LDS) unless the caller fixed a shape
     const int block = c->block > 0 ? c->block : 256;
     const int bpc = c->blocks_per_cu > 0 ? c->blocks_per_cu
-                                         : march_probe_blocks_per_cu(p.G.layout, block);
+                                         : march_probe_blocks_per_cu(p, p.G.layout, block);
     const uint64_t need = (n_rays + block - 1) / block;
     const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)bpc * c->n_cu, need));
     hipError_t e = launch_march_probe(p, p.G.layout, grid, block, (unsigned long long *)d_sum, s);

@@ -1570,7 +1570,7 @@ transport_kernel(const KParams p) {
 // interactions, energies or tallies.  Dead lanes are refilled once
 // `event_batch` of them wait.  Its step rate is the
 // ceiling of the transport's march on the same object.
-template <int MODE>
+template <int MODE, int GROUP>
 __global__ void __launch_bounds__(256) march_probe_kernel(const KParams p,
                                                           unsigned long long *sum) {
     const int lane = (int)__lane_id();
@@ -1622,11 +1622,11 @@ __global__ void __launch_bounds__(256) march_probe_kernel(const KParams p,
             continue;
         }
         if (alive) {
-            uint32_t code[kPrefetch];
-            float vr[kPrefetch];
+            uint32_t code[GROUP];
+            float vr[GROUP];
             const float kf = (float)k;
 #pragma unroll
-            for (int u = 0; u < kPrefetch; ++u) {
+            for (int u = 0; u < GROUP; ++u) {
                 if (u % 4 == 0 && u > 0) {
 #pragma unroll
                     for (int a = 0; a < 3; ++a) q[a] = c0[a] + (kf + (float)u) * G[a];
@@ -1642,16 +1642,16 @@ __global__ void __launch_bounds__(256) march_probe_kernel(const KParams p,
                 }
             }
 #pragma unroll
-            for (int a = 0; a < 3; ++a) q[a] = c0[a] + (kf + (float)kPrefetch) * G[a];
+            for (int a = 0; a < 3; ++a) q[a] = c0[a] + (kf + (float)GROUP) * G[a];
             const uint32_t rem = nsteps - k;
 #pragma unroll
-            for (int u = 0; u < kPrefetch; ++u) {
+            for (int u = 0; u < GROUP; ++u) {
                 uint32_t c = code[u];
                 if (MODE == kGeneric) c += __float_as_uint(vr[u]) & 1u;
                 acc += (uint32_t)u < rem ? c : 0u;
             }
-            taken += rem < (uint32_t)kPrefetch ? rem : (uint32_t)kPrefetch;
-            k += kPrefetch;
+            taken += rem < (uint32_t)GROUP ? rem : (uint32_t)GROUP;
+            k += GROUP;
             if (k >= nsteps) alive = false;
         }
     }
@@ -1764,17 +1764,26 @@ hipError_t launch_batch(const KParams &p, int max_lane_palette, int grid, int bl
     return hipGetLastError();
 }
 
+// f(kernel) for the march probe of an object
+template <class F>
+static void with_march_probe(const KParams &p, int layout, F f) {
+    const bool big = big_object(p, layout);
+    if (layout == kPaletteLane)
+        big ? f(march_probe_kernel<kPaletteLane, kBigGroup>)
+            : f(march_probe_kernel<kPaletteLane, kPrefetch>);
+    else if (layout == kPaletteShared)
+        big ? f(march_probe_kernel<kPaletteShared, kBigGroup>)
+            : f(march_probe_kernel<kPaletteShared, kPrefetch>);
+    else
+        big ? f(march_probe_kernel<kGeneric, kBigGroup>)
+            : f(march_probe_kernel<kGeneric, kPrefetch>);
+}
+
 hipError_t launch_march_probe(const KParams &p, int layout, int grid, int block,
                               unsigned long long *sum, hipStream_t stream) {
-    if (layout == kPaletteLane)
-        hipLaunchKernelGGL(march_probe_kernel<kPaletteLane>, dim3(grid), dim3(block), 0, stream,
-                           p, sum);
-    else if (layout == kPaletteShared)
-        hipLaunchKernelGGL(march_probe_kernel<kPaletteShared>, dim3(grid), dim3(block), 0,
-                           stream, p, sum);
-    else
-        hipLaunchKernelGGL(march_probe_kernel<kGeneric>, dim3(grid), dim3(block), 0, stream, p,
-                           sum);
+    with_march_probe(p, layout, [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), 0, stream, p, sum);
+    });
     return hipGetLastError();
 }
 
@@ -2072,17 +2081,11 @@ static int occupancy(int block, size_t lds, bool stats, bool pd, bool bind, bool
                  : occ_k<MODE, BATCH, false, false>(block, lds, bind);
 }
 
-int march_probe_blocks_per_cu(int layout, int block) {
+int march_probe_blocks_per_cu(const KParams &p, int layout, int block) {
     int nb = 0;
-    if (layout == kPaletteLane)
-        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, march_probe_kernel<kPaletteLane>,
-                                                           block, 0);
-    else if (layout == kPaletteShared)
-        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &nb, march_probe_kernel<kPaletteShared>, block, 0);
-    else
-        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, march_probe_kernel<kGeneric>,
-                                                           block, 0);
+    with_march_probe(p, layout, [&](auto kernel) {
+        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, block, 0);
+    });
     return nb > 0 ? nb : 1;
 }
 
