@@ -46,7 +46,7 @@ PHANTOMS = {
 }
 
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2201_13191_amd", "csrc", f)
-                  for f in ("transport.hip", "kernel_params.hpp")]
+                  for f in ("transport.hip", "kernel_params.hpp", "fp64_math.hpp")]
 
 
 def kernel_source_hash():
