@@ -500,7 +500,8 @@ mc_status mc_tally_to_float_async(mc_ctx *ctx, const int64_t *d_in, float *d_out
 /* Savitzky-Golay smoothing (the paper uses cubic order): least-squares
  * polynomial of degree `order` over `window` (odd, <= 31) samples, applied
  * along rows then columns, samples beyond an edge mirrored about the edge
- * sample.  d_tmp: caller scratch of nx*ny floats.  fp32. */
+ * sample.  d_tmp: caller scratch of nx*ny floats, used where d_in and d_out
+ * overlap (smoothing in place).  fp32. */
 mc_status mc_savgol_async(mc_ctx *ctx, const float *d_in, float *d_out, float *d_tmp, int nx,
                           int ny, int window, int order, void *stream);
 /* Cubic up-sampling by an integer factor (the paper's (576,800) -> (2304,3200)

@@ -1474,8 +1474,8 @@ mc_status mc_fdk_async(mc_ctx *c, const float *d_proj, int n_ang, float *d_tmp, 
     if (!d_proj || !d_tmp || !d_vol || n_ang < 1 || nx < 1 || ny < 1 || nz < 1 ||
         !(voxel_mm > 0.0f) || (int64_t)nx * ny * nz >= ((int64_t)1 << 31))
         return fail(c, MC_E_INVALID_ARG, "bad reconstruction arguments");
-    // LDS: one panel row (fp64) per filter block, cos/sin of every angle per
-    // backprojection block, 64 KiB each at most
+    // LDS: one panel row (fp64) per block of the row-wise filter, cos/sin of every
+    // angle per backprojection block, 64 KiB each at most
     if (c->g.nu > 8192 || n_ang > 4096)
         return fail(c, MC_E_INVALID_ARG, "FDK supports nu <= 8192 and n_ang <= 4096");
     // every voxel strictly inside the source orbit (the distance weight's

@@ -15,19 +15,26 @@
 //
 // Reproducibility: every photon owns a Philox4x32-10 stream (key = seed,
 // counter = photon id, draw index / 4), all fp32 state is updated with
-// separately rounded operations (built with -ffp-contract=off), the samplers
-// decide as correctly rounded fp64 + - * / would and round once, transcendentals
-// and the samplers' quotients are fp64 (fp64_math.hpp) rounded to fp32, and
-// tallies are int64 fixed point added with atomics.
+// separately rounded operations (built with -ffp-contract=off),
+// transcendentals and the samplers' quotients are fp64, and
+// tallies are int64 fixed point added with atomics.  A photon's history therefore
+// does not depend on which lane, wave or round runs it, and images do not depend
+// on the launch shape.  Kahn's acceptance is that of correctly rounded fp64
+// + - * /; the other quotients, roots and transcendentals are within an ulp or
+// two of fp64 (fp64_math.hpp) before they are rounded to fp32 or compared with a
+// draw, so that a result next to a rounding boundary may differ from correctly
+// rounded fp64's by the last bit of fp32 (the Rayleigh cosine most easily: at 1 keV 2 / (b V)
+// amplifies its quotient's error about a hundredfold, to some 2^-45).  Agreement
+// with the oracle, which divides exactly, is therefore measured (the parity tests ask
+// for the same bits) and not given by construction.
 //
-// Vector instructions bound it (80 % of the issue slots at 512^3, 19 of 64
+// Vector instructions bound it (82 % of the issue slots at 512^3, 21 of 64
 // lanes active on average), so instructions are what the event code saves:
 // elementary functions of the few arguments that occur, acceptance tests on
 // approximate reciprocals, the cross sections of a material in two 16-byte
 // loads, the Philox key schedule on the scalar unit.  2e7 photons through 256^3
 // 3.83 -> 3.46 ms, 2e8 through 512^3 42.7 -> 40.7 ms, a batch of 45 angles
-// 6.97 -> 6.24 ms, 1e6 point-detector photons 3.15 -> 2.93 ms.  A photon's history therefore does not depend on which lane,
-// wave or round runs it, and images do not depend on the launch shape.
+// 6.97 -> 6.24 ms, 1e6 point-detector photons 3.15 -> 2.93 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -447,8 +454,9 @@ __device__ __forceinline__ bool panel_hit(const KParams &p, const ProjFrame &F, 
     return true;
 }
 
-// i / b by inv = 1 / b (fp32): pixels are below 2^14, so (i + 1/2) / b is at least
-// 2^-15 from a whole number, and the product's error below 2^-9
+// i / b by inv = 1 / b (fp32): (i + 1/2) / b is at least 1 / (2 b) from a whole number,
+// and with pixels below 2^14 the product's error, two roundings of at most 2^14 / b, is
+// below 2^-8 of that
 __device__ __forceinline__ int bin_of(int i, float inv) { return (int)(((float)i + 0.5f) * inv); }
 
 // birth direction inside the cone that circumscribes the panel: cos theta

@@ -43,9 +43,10 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
 
 // Blocks go to the 8 XCDs in turn, each with its own L2.  The rank of a block
 // among all when those of one XCD come first: consecutive ranks run on one XCD,
-// so that blocks with common inputs (neighbouring rows, the tiles of one pixel
-// range) find them in its L2 (a forward pass of the network on 8 maps of 128^2,
-// whose convolutions read every row in three blocks: 318 -> 300 us).
+// so that blocks with common inputs find them in its L2 (a forward pass of the
+// network on 8 maps of 128^2, whose convolutions read every row in three blocks:
+// 318 -> 300 us).  Of a grid's x alone it orders the blocks of one y: neighbouring
+// pixel tiles, not (unless x is a multiple of 8) the channel tiles of one pixel range.
 constexpr uint32_t kXcds = 8;
 __device__ __forceinline__ uint32_t xcd_rank(uint32_t block, uint32_t blocks) {
     const uint32_t xcd = block % kXcds, each = blocks / kXcds, more = blocks % kXcds;
@@ -601,7 +602,7 @@ constexpr size_t conv_lds_split_bytes() {
 // the next four chunks' loads in flight, where conv3x3_lds_split_kernel's waves
 // load 32 bytes of each line by themselves (an L1 access each, and the lines
 // again from the L2: 8 x 32^2, 384 -> 128 channels 24.4 -> 20.1 us, 8 x 16^2,
-// 256 -> 256 15.1 -> 11.3).  Sums are added in the same order.
+// 256 -> 256 15.1 -> 11.3).  Sums are added in the same order.  cin is a multiple of 64.
 template <int WM>
 constexpr int shared_in_elems() { return (3 * (32 * WM + 2) + 1) * 16; }  // one chunk's window
 constexpr int kSharedWElems = (9 * 32 + 1) * 16;   // and its weights (16 more: the chunks' banks)
@@ -638,7 +639,6 @@ __global__ void __launch_bounds__(256) conv3x3_lds_shared_kernel(const ConvArgs 
         const int ry = wide ? 0 : j / a.w_;
         aoff[i] = ry * wn + (j - ry * (wide ? 0 : a.w_));
     }
-    const int kc = a.cin >> 4;
     const size_t wk = (size_t)9 * a.cin;
     f32x16 acc[WM][1];
 #pragma unroll
@@ -657,24 +657,21 @@ __global__ void __launch_bounds__(256) conv3x3_lds_shared_kernel(const ConvArgs 
     }
     uint4 rin[kInPer], rw[kWPer];
     auto load_group = [&](int g) __attribute__((always_inline)) {
-        const bool have = g * KS + chunk < kc;
 #pragma unroll
         for (int m = 0; m < kInPer; ++m) {
             rin[m] = make_uint4(0u, 0u, 0u, 0u);
-            if (pix[m] >= 0 && have)
+            if (pix[m] >= 0)
                 rin[m] = *(const uint4 *)(a.x + (size_t)pix[m] * a.ldx + a.xoff + g * KS * 16 +
                                           sub * 8);
         }
 #pragma unroll
         for (int m = 0; m < kWPer; ++m) {
             const int rest = (threadIdx.x >> 3) + 32 * m, col = rest & 31, tap = rest >> 5;
-            rw[m] = make_uint4(0u, 0u, 0u, 0u);
-            if (have)
-                rw[m] = *(const uint4 *)(a.w + (size_t)(co0 + col) * wk + (size_t)tap * a.cin +
-                                         g * KS * 16 + sub * 8);
+            rw[m] = *(const uint4 *)(a.w + (size_t)(co0 + col) * wk + (size_t)tap * a.cin +
+                                     g * KS * 16 + sub * 8);
         }
     };
-    const int groups = (kc + KS - 1) / KS;
+    const int groups = a.cin / (16 * KS);
     load_group(0);
     for (int g = 0; g < groups; ++g) {
 #pragma unroll
@@ -688,22 +685,18 @@ __global__ void __launch_bounds__(256) conv3x3_lds_shared_kernel(const ConvArgs 
                        (sub & 1) * 8) = rw[m];
         __syncthreads();
         if (g + 1 < groups) load_group(g + 1);        // in flight during the products
-        if (g * KS + ks < kc) {
-            const uint16_t *win = in + ks * kIn, *wm = wl + ks * kSharedWElems;
+        const uint16_t *win = in + ks * kIn, *wm = wl + ks * kSharedWElems;
 #pragma unroll
-            for (int r = 0; r < 3; ++r)
+        for (int r = 0; r < 3; ++r)
 #pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    const bf16x8 bv = *(const bf16x8 *)(wm + ((3 * r + k) * 32 + lr) * 16 + kh * 8);
+            for (int k = 0; k < 3; ++k) {
+                const bf16x8 bv = *(const bf16x8 *)(wm + ((3 * r + k) * 32 + lr) * 16 + kh * 8);
 #pragma unroll
-                    for (int i = 0; i < WM; ++i) {
-                        const bf16x8 av =
-                            *(const bf16x8 *)(win + (aoff[i] + r * wn + k) * 16 + kh * 8);
-                        acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[i][0], 0,
-                                                                            0, 0);
-                    }
+                for (int i = 0; i < WM; ++i) {
+                    const bf16x8 av = *(const bf16x8 *)(win + (aoff[i] + r * wn + k) * 16 + kh * 8);
+                    acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[i][0], 0, 0, 0);
                 }
-        }
+            }
         __syncthreads();      // the next chunks overwrite these
     }
     // partial tiles of waves 1 .. 3 over the chunks (no longer read), [ks-1][register][lane]
