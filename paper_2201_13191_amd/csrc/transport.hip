@@ -34,7 +34,8 @@
 // approximate reciprocals, the cross sections of a material in two 16-byte
 // loads, the Philox key schedule on the scalar unit.  2e7 photons through 256^3
 // 3.83 -> 3.46 ms, 2e8 through 512^3 42.7 -> 40.7 ms, a batch of 45 angles
-// 6.97 -> 6.24 ms, 1e6 point-detector photons 3.15 -> 2.93 ms.
+// 6.97 -> 6.24 ms, 1e6 point-detector photons 3.15 -> 2.93 ms (each pair on one card;
+// cards differ by some percent).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -753,7 +754,7 @@ transport_kernel(const KParams p) {
     // so that a wave evaluates 64 at a time and the ones roulette removes do
     // not hold up the others (each lane looping over its own photon's left 5.9
     // of 64 lanes active, now 17.4; 1e6 photons, split 20, 1 keV roulette:
-    // 3.15 -> 0.92 ms).  pd_wait: the lane's photon waits at a
+    // 3.43 -> 0.95 ms).  pd_wait: the lane's photon waits at a
     // scattering, 1 to be listed, 2 with pairs left to hand out, 3 with all of
     // them taken (it scatters once its lane is free).  The listed photons'
     // lanes are ranked, Compton events first: lane r's pd_src is the lane of

@@ -667,8 +667,11 @@ __global__ void __launch_bounds__(256) conv3x3_lds_shared_kernel(const ConvArgs 
 #pragma unroll
         for (int m = 0; m < kWPer; ++m) {
             const int rest = (threadIdx.x >> 3) + 32 * m, col = rest & 31, tap = rest >> 5;
-            rw[m] = *(const uint4 *)(a.w + (size_t)(co0 + col) * wk + (size_t)tap * a.cin +
-                                     g * KS * 16 + sub * 8);
+            // (word by word: copied whole without a condition, the array is kept in
+            // scratch memory)
+            const uint4 v = *(const uint4 *)(a.w + (size_t)(co0 + col) * wk +
+                                             (size_t)tap * a.cin + g * KS * 16 + sub * 8);
+            rw[m] = make_uint4(v.x, v.y, v.z, v.w);
         }
     };
     const int groups = a.cin / (16 * KS);
