@@ -988,28 +988,33 @@ __global__ void __launch_bounds__(64 * kWgWaves, 2) wgrad9_kernel(const WgradArg
     }
 }
 
-// dw[co][tap][ci] from the splits' partial tiles [split][tap][co][ci]: 16
-// running sums, each of every 16th split, and those in pairs
-constexpr int kWgSums = 16;
+// dw[co][tap][ci] from the splits' partial tiles [split][tap][co][ci]: N running sums,
+// each of every N-th split, and those in pairs
+constexpr int kWgSums = 16;      // N, at most
 
+template <int N>
 __global__ void __launch_bounds__(256) wgrad_sum_kernel(const float *partial, int splits, int cout,
                                                         int cin, float *dw) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int n = 9 * cout * cin;
     if (i >= n) return;
     const int ci = i % cin, co = (i / cin) % cout, tap = i / (cin * cout);
-    float s[kWgSums] = {};
+    float s[N] = {};
     int k = 0;
-    for (; k + kWgSums <= splits; k += kWgSums) {
-        float v[kWgSums];
+    for (; k + N <= splits; k += N) {
+        float v[N];
 #pragma unroll
-        for (int q = 0; q < kWgSums; ++q) v[q] = partial[(size_t)(k + q) * n + i];
+        for (int q = 0; q < N; ++q) v[q] = partial[(size_t)(k + q) * n + i];
 #pragma unroll
-        for (int q = 0; q < kWgSums; ++q) s[q] += v[q];
+        for (int q = 0; q < N; ++q) s[q] += v[q];
     }
+    if (k < splits) {
+        float v[N];
 #pragma unroll
-    for (int q = 0; q < kWgSums; ++q)
-        if (k + q < splits) s[q] += partial[(size_t)(k + q) * n + i];
+        for (int q = 0; q < N; ++q) v[q] = partial[(size_t)min(k + q, splits - 1) * n + i];
+#pragma unroll
+        for (int q = 0; q < N; ++q) s[q] += k + q < splits ? v[q] : 0.0f;
+    }
     dw[((size_t)co * 9 + tap) * cin + ci] = sum_pairs(s);
 }
 
@@ -1393,19 +1398,19 @@ constexpr int kWgBlocks = 256;
 // 252 blocks 18.5 us, 264 30.6, 516 of half as many waves 34) with at least 4 slices a
 // wave, or as many rounds of that as keep the rounding error to what the caller's splits
 // give in the other kernel's order (4 waves, then 32 splits, then the groups, each in a
-// row).  The error's variance goes with the terms that are added in a row, and with twice
-// the levels of a sum in pairs; a slice's products go to the accumulator in two halves,
-// each rounded (fp32 sums made in that order on the host have the kernel's very error).
-// 4 x 128^2, 512 -> 64 channels, 32 splits for the caller: one round (8 splits) has 1.18
-// times the rms error of that order, two have 0.91 of it.
+// row).  Of m equal terms added one after the other the rounding errors' variance is that
+// of m + 1 - 2 / m roundings of half the sum, in pairs that of two a level; a
+// slice's products go to the accumulator in two halves, each rounded (fp32 sums made in
+// that order on the host have the kernel's very error).  4 x 128^2, 512 -> 64 channels, 32
+// splits for the caller: one round (8 splits) has 1.18 times the rms error of that order,
+// two have 0.85 of it.
 static int wgrad9_splits(int64_t slices, int64_t tiles, int caller) {
-    auto up = [](int64_t x, int64_t y) { return (x + y - 1) / y; };
-    auto row = [](int64_t m) { return m > 1 ? m : 0; };
-    const int64_t most = 2 * up(slices, 4LL * caller) + 4 + row(std::min(caller, kWgGroup)) +
-                         row(up(caller, kWgGroup));
+    auto row = [](double m) { return m > 1.0 ? m + 1.0 - 2.0 / m : 0.0; };
+    const double most = row(2.0 * slices / (4.0 * caller)) + row(4.0) +
+                        row(std::min(caller, kWgGroup)) + row((double)caller / kWgGroup);
     auto ours = [&](int64_t k) {
-        const int64_t pairs = k > 8 ? 8 : k > 4 ? 6 : k > 2 ? 4 : k > 1 ? 2 : 0;
-        return 2 * up(slices, kWgWaves * k) + 6 + row(up(k, kWgSums)) + pairs;
+        const double pairs = k > 8 ? 8.0 : k > 4 ? 6.0 : k > 2 ? 4.0 : k > 1 ? 2.0 : 0.0;
+        return row(2.0 * slices / (double)(kWgWaves * k)) + 6.0 + row((double)k / kWgSums) + pairs;
     };
     int64_t s = std::min<int64_t>(std::max<int64_t>(1, kWgBlocks / tiles), slices / (4 * kWgWaves));
     s = std::max<int64_t>(1, std::min<int64_t>(s, caller));
@@ -1423,8 +1428,17 @@ hipError_t nn_wgrad(const WgradArgs &a, float *tmp, float *dw, hipStream_t s) {
         const int splits = wgrad9_splits((int64_t)a.n * a.h * (a.w_ / 16), tiles, a.splits);
         hipLaunchKernelGGL(wgrad9_kernel, dim3(tiles * splits), dim3(64 * kWgWaves), 0, s, a,
                            splits);
-        hipLaunchKernelGGL(wgrad_sum_kernel, dim3(blocks_for((int64_t)9 * a.cout * a.cin)),
-                           dim3(256), 0, s, (const float *)a.partial, splits, a.cout, a.cin, dw);
+        auto sum = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(blocks_for((int64_t)9 * a.cout * a.cin)), dim3(256), 0,
+                               s, (const float *)a.partial, splits, a.cout, a.cin, dw);
+        };
+        // as many sums as the splits can use (each is a load, used or not)
+        if (splits == 1)
+            sum(wgrad_sum_kernel<1>);
+        else if (splits <= 4)
+            sum(wgrad_sum_kernel<4>);
+        else
+            sum(wgrad_sum_kernel<kWgSums>);
         return hipGetLastError();
     } else {
         const dim3 grid((a.cout + 31) / 32, 9 * ((a.cin + 31) / 32), a.splits);
