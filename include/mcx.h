@@ -359,8 +359,9 @@ mc_status mc_project_batch_static(mc_ctx *ctx, const mc_job *jobs, int n_jobs, i
  * generic layout) to d_sum[0] and the number of steps taken to d_sum[1]
  * (device uint64[2], not cleared).  Stream-ordered; the block size and
  * blocks per compute unit of mc_set_launch apply, and automatic blocks per
- * CU means the probe's own occupancy.  Its step rate is the ceiling of the
- * transport's march on the same object. */
+ * CU means the probe's own occupancy.  Its step rate is what the transport's
+ * march on the same object is reported against (not a ceiling: whole chords
+ * gather with less locality than flights that end at interactions). */
 mc_status mc_march_probe_async(mc_ctx *ctx, float angle_rad, uint64_t n_rays, uint64_t seed,
                                int refill_batch, uint64_t *d_sum, void *stream);
 

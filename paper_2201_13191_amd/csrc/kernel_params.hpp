@@ -29,7 +29,10 @@ struct ProjFrame {
 // the xy plane and most steps are taken within a few degrees of it, so such
 // rays cross fewer lines (2e8 photons through 512^3, bound by the lines fetched
 // beyond the L2: 8 x 4 x 4 41.98 ms, 8 x 8 x 2 40.78, 16 x 8 x 1 44.9; objects
-// that fit the caches take the same with each).
+// that fit the caches take the same with each).  Steep cones pay for it: with a source
+// at the edge of the object, 45 degrees to the panel's rim and noise throughout, 4e6
+// photons through 448^3 take 1.25 ms in 8 x 4 x 4 and 1.31 in 8 x 8 x 2 (ids and
+// densities 6.35 and 6.48).
 constexpr int kBx = 8, kBy = 8, kBz = 2;
 constexpr int kBrick = kBx * kBy * kBz;
 // When it fits the 24-bit brick strides, a bricked object extends kEdgePad

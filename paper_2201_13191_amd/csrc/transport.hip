@@ -1577,8 +1577,9 @@ transport_kernel(const KParams p) {
 // centres, clamps, layout and prefetch groups, adding up the codes it
 // gathers (sum[0]) and the steps it takes (sum[1]); no optical depth,
 // interactions, energies or tallies.  Dead lanes are refilled once
-// `event_batch` of them wait.  Its step rate is the
-// ceiling of the transport's march on the same object.
+// `event_batch` of them wait.  Its step rate is what the transport's march on the same
+// object is reported against (no ceiling: its whole chords gather with less locality
+// than flights that end at interactions).
 template <int MODE, int GROUP>
 __global__ void __launch_bounds__(256) march_probe_kernel(const KParams p,
                                                           unsigned long long *sum) {
