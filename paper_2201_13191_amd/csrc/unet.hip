@@ -1398,10 +1398,10 @@ constexpr int kWgBlocks = 256;
 // 252 blocks 18.5 us, 264 30.6, 516 of half as many waves 34) with at least 4 slices a
 // wave, or as many rounds of that as keep the rounding error to what the caller's splits
 // give in the other kernel's order (4 waves, then 32 splits, then the groups, each in a
-// row).  Of m equal terms added one after the other the rounding errors' variance is that
-// of m + 1 - 2 / m roundings of half the sum, in pairs that of two a level; a
-// slice's products go to the accumulator in two halves, each rounded (fp32 sums made in
-// that order on the host have the kernel's very error).  4 x 128^2, 512 -> 64 channels, 32
+// row).  Of m random terms added one after the other the rounding errors' variance is
+// (m + 1 - 2 / m) / 2 times that of rounding the sum once, in pairs 1 a level (counted in
+// halves here); a slice's products go to the accumulator in two halves, each rounded (fp32
+// sums made in that order on the host have the kernel's very error).  4 x 128^2, 512 -> 64 channels, 32
 // splits for the caller: one round (8 splits) has 1.18 times the rms error of that order,
 // two have 0.85 of it.
 static int wgrad9_splits(int64_t slices, int64_t tiles, int caller) {
